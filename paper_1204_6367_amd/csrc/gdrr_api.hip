@@ -500,7 +500,6 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         if (B.only_volume < 0 || B.jobs[k].volume == B.only_volume) total_photons += B.jobs[k].n_photons;
     bool local = false;
     for (int v = 0; v < B.n_vols; ++v) local |= B.vols[v].macro > 0;
-    const int block = tune.block ? tune.block : 256;
     // the single-majorant tables are staged only if some traced volume tracks with them
     bool any_single = false;
     for (int v = 0; v < B.n_vols; ++v) any_single |= batch_uses(B, v) && B.vols[v].macro <= 0;
@@ -537,11 +536,21 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // as keep the workgroups per compute unit that the launch has without them (or the tuned
     // count), as the runtime's occupancy calculation has it.
     const int n_mat = phys->n_mat;
+    // Default shape.  All-local launches are bound by VALU issue: they gain from early refills
+    // and from 1024-thread workgroups, two per compute unit, which share the tables and cube
+    // records and so keep 8 wavefronts per SIMD (2e7 photons of a 256x256x160 phantom: 3.44 ms
+    // against 5.18 at 256 threads and deferral 32; 3.5 against 5.1 to 5.3 from 32x32x20 to
+    // 512x512x256).  A launch with a single-majorant volume waits on its gathers, where late
+    // refills do best (512x512x256: 3.21 ms against 3.50).
+    // (The trace kernel runs 6 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
+    const bool wide = local_kind == 3 && B.mode != kModeTrace;
+    int block = tune.block ? tune.block : (wide ? 1024 : 256);
     const auto lds_for = [&](int rows) {
         return draw_slots_offset_bytes(table_floats2(rows, phys->n_e, n_maj) * 8 +
                                        (size_t)macro_lds_n * lds_record_bytes(local_kind)) +
                (size_t)block * 16;
     };
+    while (!tune.block && block > 256 && lds_for(n_mat) > dev.lds_max) block /= 2;   // (16 bytes a thread)
     const void* mfunc = mc_func_for(B.mode, local_kind);
     // (the LDS of a workgroup is allocated in granules of kLdsGranule bytes, which the
     // runtime's occupancy calculation does not round to: the query gets the rounded size)
@@ -582,8 +591,8 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         c = std::max<unsigned long long>(64, std::min<unsigned long long>(4096, c));
         chunk = (int)(c / 64 * 64);
     }
-    const int defer = tune.defer ? tune.defer : 32;
-    const int cdefer = tune.coll_defer ? tune.coll_defer : defer;
+    const int defer = tune.defer ? tune.defer : (wide ? 8 : 32);
+    const int cdefer = tune.coll_defer ? tune.coll_defer : (wide && !tune.defer ? 12 : defer);
 
     const size_t n_jobs = (size_t)B.n_jobs;
     const size_t job_bytes = sizeof(unsigned long long) * (n_jobs + 1);
@@ -1222,11 +1231,12 @@ int gdrr_last_kernel_ms(float* ms) {
 
 int gdrr_default_tuning(gdrr_tuning* out) {
     if (!out) return fail(GDRR_EINVAL, "out is NULL");
-    out->block = 256;
+    // (of launches whose volumes all track with local majorants from LDS; others 256, 32, 32)
+    out->block = 1024;
     out->blocks_per_cu = 0;
     out->chunk = 0;
-    out->defer = 32;
-    out->coll_defer = 0;
+    out->defer = 8;
+    out->coll_defer = 12;
     return GDRR_OK;
 }
 
