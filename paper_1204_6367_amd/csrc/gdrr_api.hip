@@ -545,12 +545,12 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // (The trace kernel runs 6 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
     const bool wide = local_kind == 3 && B.mode != kModeTrace;
     int block = tune.block ? tune.block : (wide ? 1024 : 256);
+    int n_slots = 64;
     const auto lds_for = [&](int rows) {
-        return draw_slots_offset_bytes(table_floats2(rows, phys->n_e, n_maj) * 8 +
-                                       (size_t)macro_lds_n * lds_record_bytes(local_kind)) +
-               (size_t)block * 16;
+        return slots_offset_bytes(table_floats2(rows, phys->n_e, n_maj) * 8 +
+                                  (size_t)macro_lds_n * lds_record_bytes(local_kind)) +
+               (size_t)(block / 64) * n_slots * slot_bytes(local_kind);
     };
-    while (!tune.block && block > 256 && lds_for(n_mat) > dev.lds_max) block /= 2;   // (16 bytes a thread)
     const void* mfunc = mc_func_for(B.mode, local_kind);
     // (the LDS of a workgroup is allocated in granules of kLdsGranule bytes, which the
     // runtime's occupancy calculation does not round to: the query gets the rounded size)
@@ -560,6 +560,20 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mfunc, block, held));
         return GDRR_OK;
     };
+    // Started photons per wavefront: 64 (a full wavefront starts them), or min_slots() where 64
+    // would not fit the LDS of a workgroup or would cost a workgroup per compute unit (8 against 6
+    // wavefronts per SIMD is worth 5 %, full wavefronts of starts less).
+    {
+        int nb_full = 0, nb_few = 0;
+        const bool fits = lds_for(n_mat) <= dev.lds_max;
+        if (fits && (rc = per_cu_with(lds_for(n_mat), nb_full))) return rc;
+        n_slots = min_slots(local_kind);
+        while (!tune.block && block > 256 && lds_for(n_mat) > dev.lds_max) block /= 2;
+        if (fits) {
+            if ((rc = per_cu_with(lds_for(n_mat), nb_few))) return rc;
+            if (nb_few <= nb_full || (tune.blocks_per_cu && tune.blocks_per_cu <= nb_full)) n_slots = 64;
+        }
+    }
     int mask_rows = 0;
     if (local_kind == 3 && n_mat <= 8 && lds_for(n_mat) <= dev.lds_max) {
         int target = tune.blocks_per_cu;
@@ -782,6 +796,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     kp.grad = B.grad;
     for (int v = 0; v < kMaxVol; ++v) kp.macro_lds[v] = v < GDRR_MAX_VOLUMES ? macro_lds[v] : -1;
     kp.macro_lds_n = macro_lds_n;
+    kp.n_slots = n_slots;
     const void* mf = mc_func_for(B.mode, local_kind);
     int timed = -1;
     if (chunks > 0) {

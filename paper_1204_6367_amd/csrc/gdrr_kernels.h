@@ -55,6 +55,7 @@ struct KParams {
     // local majorants staged in LDS after the tables: per volume the offset (records) or -1
     int macro_lds[kMaxVol];
     int macro_lds_n;          // records staged in total
+    int n_slots;              // started photons a wavefront keeps in LDS
 };
 
 // LDS holds what every free flight reads: the total attenuation per
@@ -72,11 +73,16 @@ __host__ __device__ inline size_t table_floats2(int tot_rows, int n_e, int n_maj
 // the others the record as built.
 __host__ __device__ inline size_t lds_record_bytes(int local_kind) { return local_kind == 3 ? 4 : 8; }
 
-// Per wavefront, after the tables and cube records: 64 slots of source draws
-// (16 bytes each), starting at a 16-byte boundary.
-__host__ __device__ inline size_t draw_slots_offset_bytes(size_t tables_and_records_bytes) {
+// Per wavefront, after the tables and cube records: slots of started photons,
+// from a 16-byte boundary.  A slot is two 16-byte words (position and energy;
+// direction and aim pixel) and, where a volume may track with a single
+// majorant, the distance left to the box (4 bytes).  64 slots a wavefront, or
+// min_slots() (at most 1 KiB a wavefront) where the LDS does not hold them.
+__host__ __device__ inline size_t slots_offset_bytes(size_t tables_and_records_bytes) {
     return (tables_and_records_bytes + 15) & ~(size_t)15;
 }
+__host__ __device__ inline uint32_t slot_bytes(int local_kind) { return local_kind == 3 ? 32u : 36u; }
+__host__ __device__ inline int min_slots(int local_kind) { return local_kind == 3 ? 32 : 16; }   // (powers of two)
 
 // The row field of an all-local LDS record: 31 = no row (the bound then comes
 // from the cube's material mask in its global record).
@@ -167,61 +173,68 @@ struct Photon {
     double w;                  // adjoint weight of the history
 };
 
-// Source photon (Sec. 2.1/2.4), in two parts.  The draw: aim pixel and energy
-// channel by inverse CDF (the energy from the row of the pixel's column for a
-// joint source) and the two jitter words, from photon `pid`'s step-0 blocks
-// alone, so that a wavefront can draw for the next photons of its chunk all at
-// once.  Returns (pixel, channel, jitter word u, jitter word v).
-__device__ __forceinline__ uint4 draw_source(const KParams& P, int job, uint32_t pid) {
-    const DJob& J = P.jobs[job];
+// Source photon (Sec. 2.1/2.4): aim pixel and energy channel by inverse CDF
+// (the energy from the row of the pixel's column for a joint source), aim
+// point uniform inside the pixel, straight line from S to the phantom.  It
+// depends on the photon index alone, so that a wavefront can start the next
+// photons of its chunk all at once.  in: the photon enters the phantom;
+// otherwise it reaches its aim pixel unscattered.
+struct Start {
+    float px, py, pz, dx, dy, dz, E, trem;
+    int pix;
+    bool in;
+};
+
+__device__ __forceinline__ Start start_state(const KParams& P, const DJob& J, const DVolume& V, uint32_t pid) {
     const DSource& S = P.src[J.src];
     const Block b0 = philox(pid, J.job_id, 0u, 0u, P.k0, P.k1);
     const Block b1 = philox(pid, J.job_id, 0u, 1u, P.k0, P.k1);
     const int kf = sample_cdf(S.flu_cdf, S.flu_guide, S.npix, S.flu_k, u53(b0.z, b0.w));
-    const int iu = kf - (kf / J.nu) * J.nu;
+    const int iv = kf / J.nu, iu = kf - iv * J.nu;
     const int row = S.spec_rows > 1 ? iu : 0;
     const int ke = sample_cdf(S.spec_cdf + (size_t)row * S.n_spec, S.spec_guide + (size_t)row * S.spec_k, S.n_spec,
                               S.spec_k, u53(b0.x, b0.y));
-    return make_uint4((uint32_t)kf, (uint32_t)ke, b1.x, b1.y);
-}
-
-// The rest of the start: aim point uniform inside the pixel, straight line from
-// S to the phantom.  Returns true if the photon enters the phantom; otherwise
-// it reaches its aim pixel unscattered.
-__device__ __forceinline__ bool start_from_draw(const KParams& P, const Tables& T, const DVolume& V, int vol_off,
-                                                Photon& ph, uint4 d) {
-    const DJob& J = P.jobs[ph.job];
-    const DSource& S = P.src[J.src];
-    const int kf = (int)d.x, ke = (int)d.y;
-    const int iv = kf / J.nu, iu = kf - iv * J.nu;
-    const float uc = ((float)iu + u24(d.z) - 0.5f * (float)J.nu) * J.du;
-    const float vc = ((float)iv + u24(d.w) - 0.5f * (float)J.nv) * J.dv;
+    const float uc = ((float)iu + u24(b1.x) - 0.5f * (float)J.nu) * J.du;
+    const float vc = ((float)iv + u24(b1.y) - 0.5f * (float)J.nv) * J.dv;
+    Start s;
     float dx = J.Px + uc * J.ux - J.Sx;
     float dy = J.Py + uc * J.uy - J.Sy;
     float dz = J.Pz + uc * J.uz + vc - J.Sz;
     const float inv = __builtin_amdgcn_rsqf(dx * dx + dy * dy + dz * dz);
     dx *= inv; dy *= inv; dz *= inv;
-    ph.dx = dx; ph.dy = dy; ph.dz = dz;
-    ph.E = fminf(fmaxf(S.spec_e[ke], P.e0), P.e_max);
-    ph.ec = energy_cache(P, T, vol_off, ph.E);
+    s.dx = dx; s.dy = dy; s.dz = dz;
+    s.E = fminf(fmaxf(S.spec_e[ke], P.e0), P.e_max);
+    s.pix = kf;
+    s.px = s.py = s.pz = s.trem = 0.0f;
+    float tin, tout;
+    s.in = box_entry(V, J.Sx, J.Sy, J.Sz, dx, dy, dz, tin, tout);
+    if (s.in) {
+        s.px = J.Sx + tin * dx;
+        s.py = J.Sy + tin * dy;
+        s.pz = J.Sz + tin * dz;
+        s.trem = tout - tin;
+    }
+    return s;
+}
+
+// A lane takes a started photon.
+__device__ __forceinline__ void take_start(const KParams& P, const Tables& T, int vol_off, Photon& ph, const Start& s) {
+    ph.px = s.px; ph.py = s.py; ph.pz = s.pz;
+    ph.dx = s.dx; ph.dy = s.dy; ph.dz = s.dz;
+    ph.E = s.E;
+    ph.trem = s.trem;
+    ph.ec = energy_cache(P, T, vol_off, s.E);
     ph.step = 0;
     ph.pair = 0;
     ph.nsc = 0;
-    ph.pix0 = kf;
-    float tin, tout;
-    if (box_entry(V, J.Sx, J.Sy, J.Sz, dx, dy, dz, tin, tout)) {
-        ph.px = J.Sx + tin * dx;
-        ph.py = J.Sy + tin * dy;
-        ph.pz = J.Sz + tin * dz;
-        ph.trem = tout - tin;
-        return true;
-    }
-    return false;
+    ph.pix0 = s.pix;
 }
 
 __device__ __forceinline__ bool start_photon(const KParams& P, const Tables& T, const DVolume& V, int vol_off,
                                              Photon& ph) {
-    return start_from_draw(P, T, V, vol_off, ph, draw_source(P, ph.job, ph.pid));
+    const Start s = start_state(P, P.jobs[ph.job], V, ph.pid);
+    take_start(P, T, vol_off, ph, s);
+    return s.in;
 }
 
 // Detector hit of a photon leaving the phantom: the primary pixel for an
@@ -779,11 +792,16 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
     const Tables T = stage_tables(P, lds);
     // local majorants small enough to stage: every volume's cube records after the tables
     float2* const lds_rec = lds + table_floats2(P.tot_rows, P.n_e, P.n_maj);
-    // the source-draw slots (offset in bytes from the LDS base of the first wavefront's)
-    const uint32_t slots_off = (uint32_t)draw_slots_offset_bytes(
+    // the slots of started photons (offset in bytes from the LDS base of the first wavefront's)
+    const uint32_t slots_off = (uint32_t)slots_offset_bytes(
         table_floats2(P.tot_rows, P.n_e, P.n_maj) * 8 + (size_t)P.macro_lds_n * lds_record_bytes(LOCAL));
-    // this wavefront's slots (wavefront-uniform)
-    const uint32_t draws_off = __builtin_amdgcn_readfirstlane((int)(slots_off + (threadIdx.x & ~63u) * 16u));
+    // this wavefront's slots (wavefront-uniform): position words, direction words, distances
+    const uint32_t n_slots = (uint32_t)P.n_slots;
+    const uint32_t wave_off =
+        __builtin_amdgcn_readfirstlane((int)(slots_off + (threadIdx.x >> 6) * n_slots * slot_bytes(LOCAL)));
+    float4* const slot_p = reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + wave_off);
+    float4* const slot_d = slot_p + n_slots;
+    float* const slot_t = reinterpret_cast<float*>(slot_d + n_slots);
     if (LOCAL == 3) {
         // (the slots serve as scratch until the transport starts)
         stage_records_rows(P, lds, reinterpret_cast<uint32_t*>(lds_rec),
@@ -813,9 +831,10 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
     ph.pair = 0u;
     ph.pm = 0;
 
-    // wavefront-uniform dispenser state; the draw slots hold photons [d_first, d_end) of the chunk
+    // wavefront-uniform dispenser state; the slots hold photons [w_next, d_end) of the chunk,
+    // photon i in slot i mod n_slots
     int w_vol = -1, w_job = 0, w_hold = 0, w_done = 0;
-    uint32_t w_next = 0, w_end = 0, d_first = 0, d_end = 0;
+    uint32_t w_next = 0, w_end = 0, d_end = 0;
 
     for (;;) {
         const uint64_t dead = __ballot(ph.st == kDead);
@@ -853,7 +872,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                     // photon indices J.first + [first, last); J.first + nph < 2^32
                     w_next = (uint32_t)__builtin_amdgcn_readfirstlane((int)(J.first + (uint32_t)first));
                     w_end = (uint32_t)__builtin_amdgcn_readfirstlane((int)(J.first + (uint32_t)last));
-                    d_first = d_end = w_next;                  // no draws of this chunk yet
+                    d_end = w_next;                            // none of this chunk started yet
                     const int v = __builtin_amdgcn_readfirstlane(J.vol);
                     if (v != w_vol) {
                         if (n_dead == 64) w_vol = v; else w_hold = 1;
@@ -861,14 +880,36 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                 }
             }
             if (!w_done && !w_hold) {
-                // Not enough drawn photons left for the waiting lanes: every lane draws one of the
-                // chunk's next 64 photons (the draws of a photon depend on its index alone).
-                if (w_next + (uint32_t)n_dead > d_end && d_end < w_end) {
-                    const uint32_t nd = w_end - w_next < 64u ? w_end - w_next : 64u;
-                    uint4* draws = reinterpret_cast<uint4*>(reinterpret_cast<char*>(lds) + draws_off);
-                    if ((uint32_t)lane < nd) draws[lane] = draw_source(P, w_job, w_next + (uint32_t)lane);
-                    d_first = w_next;
-                    d_end = w_next + nd;
+                // Not enough started photons left for the waiting lanes: the free slots are filled
+                // with the chunk's next photons, one a lane, from the source draw to the entry into
+                // the phantom.  Started here, on (almost) full wavefronts, a refill of the few lanes
+                // that wait is two LDS reads; photons that miss the phantom are scored here, once,
+                // and marked (E < 0).  (Started by the waiting lanes themselves, with only the draw
+                // done ahead: 13.0 against 12.5 ms for 7.6e7 photons of three phantoms.)
+                if ((uint32_t)n_dead > d_end - w_next && d_end < w_end) {
+                    const uint32_t room = n_slots - (d_end - w_next);
+                    const uint32_t nd = w_end - d_end < room ? w_end - d_end : room;
+                    if ((uint32_t)lane < nd) {
+                        const DJob& J = P.jobs[w_job];
+                        const DVolume& V = P.vol[w_vol];
+                        const uint32_t pid = d_end + (uint32_t)lane;
+                        Start s = start_state(P, J, V, pid);
+                        if (!s.in) {
+                            if (MODE != kModeBackward) {       // (no collision: nothing for the adjoint)
+                                Photon q;
+                                q.pid = pid;
+                                q.job = w_job;
+                                take_start(P, T, V.lds_majorant, q, s);
+                                finish<MODE>(P, T, V, V.lds_majorant, q, kPrimary, q.pix0);
+                            }
+                            s.E = -1.0f;
+                        }
+                        const uint32_t k = pid & (n_slots - 1u);
+                        slot_p[k] = make_float4(s.px, s.py, s.pz, s.E);
+                        slot_d[k] = make_float4(s.dx, s.dy, s.dz, __int_as_float(s.pix));
+                        if (LOCAL != 3) slot_t[k] = s.trem;
+                    }
+                    d_end += nd;
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // the slots are read by other lanes
                 }
                 const uint32_t avail = d_end - w_next;
@@ -878,11 +919,14 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                     ph.job = w_job;
                     ph.jid = P.jobs[w_job].job_id;
                     ph.passb = false;
-                    const DVolume& V = P.vol[w_vol];
-                    const int vo = V.lds_majorant;
-                    const uint4* draws = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(lds) + draws_off);
-                    if (start_from_draw(P, T, V, vo, ph, draws[ph.pid - d_first])) ph.st = kFly;
-                    else finish<MODE>(P, T, V, vo, ph, kPrimary, ph.pix0);
+                    const uint32_t k = ph.pid & (n_slots - 1u);
+                    const float4 a = slot_p[k], b = slot_d[k];
+                    if (a.w >= 0.0f) {
+                        const Start s{a.x, a.y, a.z, b.x, b.y, b.z, a.w, LOCAL != 3 ? slot_t[k] : 0.0f,
+                                      __float_as_int(b.w), true};
+                        take_start(P, T, P.vol[w_vol].lds_majorant, ph, s);
+                        ph.st = kFly;
+                    }
                 }
                 w_next += (uint32_t)n_dead < avail ? (uint32_t)n_dead : avail;
             }
