@@ -47,8 +47,11 @@ __device__ __forceinline__ Block philox(uint32_t c0, uint32_t c1, uint32_t c2, u
     return Block{c0, c1, c2, c3};
 }
 
-// 23 random bits -> odd multiple of 2^-24 in (0, 1); exact in float32.
-__device__ __forceinline__ float u24(uint32_t x) { return ((float)(x >> 9) + 0.5f) * 0x1p-23f; }
+// 23 random bits k -> (k + 1/2) 2^-23, an odd multiple of 2^-24 in (0, 1), exact
+// in float32: 1 + k 2^-23 by its bit pattern, minus 1 - 2^-24 (two instructions).
+__device__ __forceinline__ float u24(uint32_t x) {
+    return __uint_as_float(__builtin_amdgcn_alignbit(0x7fu, x, 9u)) - 0x1.fffffep-1f;
+}
 
 // 53 random bits of two words -> [0, 1), exact in float64.
 __device__ __forceinline__ double u53(uint32_t a, uint32_t b) {
@@ -57,6 +60,16 @@ __device__ __forceinline__ double u53(uint32_t a, uint32_t b) {
 
 __device__ __forceinline__ float fast_log(float x) { return __builtin_amdgcn_logf(x) * 0.69314718055994531f; }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+// Correctly rounded square root of 0 or of a number in [2^-96, 2^126]: the
+// hardware's (within 1 ulp), moved to a neighbour where the residual at the
+// neighbour says so.  (sqrtf also rescales denormals, which no caller has.)
+__device__ __forceinline__ float sqrt_rn(float x) {
+    const float s = __builtin_amdgcn_sqrtf(x);
+    const float lo = __int_as_float(__float_as_int(s) - 1), hi = __int_as_float(__float_as_int(s) + 1);
+    const float rl = __builtin_fmaf(-lo, s, x), rh = __builtin_fmaf(-hi, s, x);
+    const float r = rl <= 0.0f ? lo : s;
+    return rh > 0.0f ? hi : r;
+}
 __device__ __forceinline__ float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 // -expm1(e) = 1 - exp(e) for e <= 0.  For e in [-0.47, 0] (photon energies up
 // to 150 keV in the Compton sampler) by its Taylor series to e^7 (relative
@@ -157,7 +170,7 @@ __device__ __forceinline__ int sample_cdf(const double* __restrict__ cdf, const 
 // about d: d' = ct d + st (cos e1 + sin e2) with (e1, e2, d) orthonormal;
 // e2 = (z x d)/|z x d| away from the z axis, (x x d)/|x x d| within 0.1 of it.
 __device__ __forceinline__ void rotate(float& dx, float& dy, float& dz, float ct, float r) {
-    const float st = sqrtf(fmaxf(0.0f, (1.0f - ct) * (1.0f + ct)));
+    const float st = sqrt_rn(fmaxf(0.0f, (1.0f - ct) * (1.0f + ct)));
     const float cp = cos_rev(r), sp = sin_rev(r);
     const float rxy2 = dx * dx + dy * dy;
     float e1x, e1y, e1z, e2x, e2y, e2z;
@@ -213,11 +226,11 @@ __device__ __forceinline__ bool box_entry(const DVolume& V, float sx, float sy, 
     return t0 < t1;
 }
 
-// Scattering angle of a Compton or a Rayleigh event, both by rejection with
-// one Philox block (photon, job, step, 1 + try) per try; the try's fourth word
-// is the azimuth (in revolutions).  Returns cos(theta) (1 if every try is
-// rejected).  The two samplers share the loop and its Philox block, so that a
-// wavefront holding both kinds of event generates each try's block once.
+// One try of the scattering angle of a Compton or a Rayleigh event, both by
+// rejection with one Philox block (photon, job, step, 1 + try) per try; the
+// try's fourth word is the azimuth (in revolutions).  The two samplers share
+// the Philox block.  True if the try is kept; then ct = cos(theta), E the
+// energy after the event.
 //
 // Compton, free-electron Klein-Nishina: tau = E'/E drawn from the mixture of
 // densities ~1/tau (weight ln(1+2k)) and ~tau (weight (1-tau0^2)/2) on
@@ -227,59 +240,114 @@ __device__ __forceinline__ bool box_entry(const DVolume& V, float sx, float sy, 
 // x from Gamma(2, x0/2) truncated at 1/lambda when 1/lambda >= x0, else from
 // the density ~x on [0, 1/lambda] kept with probability exp(-2x/x0); then kept
 // with probability (1 + cos^2)/2.
-__device__ __forceinline__ float scatter_angle(bool is_rayleigh, uint32_t pid, uint32_t job, uint32_t step,
-                                               uint32_t k0, uint32_t k1, float& E, float x0, float& az) {
-    // Compton constants
+__device__ __forceinline__ bool try_angle(bool is_rayleigh, uint32_t pid, uint32_t job, uint32_t step, uint32_t t,
+                                          uint32_t k0, uint32_t k1, float x0, float& E, float& ct, float& az) {
+    const Block b = philox(pid, job, step, 1u + t, k0, k1);
+    const float b0 = u24(b.x), b1 = u24(b.y), b2 = u24(b.z);
+    az = u24(b.w);
+    if (is_rayleigh) {
+        const float xmax = E * (1.0f / kHc);
+        const float ixmax = kHc * fast_rcp(E);
+        const float m2ix0 = -2.0f * fast_rcp(x0);
+        float xx;
+        bool ok;
+        if (xmax >= x0) {
+            xx = -0.5f * x0 * (fast_log(b0) + fast_log(b1));
+            ok = xx <= xmax;
+        } else {
+            xx = xmax * sqrt_rn(b0);
+            ok = b1 <= fast_exp(m2ix0 * xx);
+        }
+        const float r = xx * ixmax;
+        ct = 1.0f - 2.0f * r * r;
+        return ok && b2 <= 0.5f * (1.0f + ct * ct);
+    }
     const float k = E * (1.0f / kMeC2);
     const float tau0 = fast_rcp(1.0f + 2.0f * k);
     const float a1 = fast_log(1.0f + 2.0f * k);
     const float ik = fast_rcp(k);
     const float omt02 = 1.0f - tau0 * tau0;
     const float a2 = 0.5f * omt02;
-    // Rayleigh constants
-    const float xmax = E * (1.0f / kHc);
-    const float ixmax = kHc * fast_rcp(E);
-    const float m2ix0 = -2.0f * fast_rcp(x0);
-    for (int t = 0; t < kMaxTries; ++t) {
-        const Block b = philox(pid, job, step, 1u + (uint32_t)t, k0, k1);
-        const float b0 = u24(b.x), b1 = u24(b.y), b2 = u24(b.z);
-        az = u24(b.w);
-        if (is_rayleigh) {
-            float xx;
-            bool ok;
-            if (xmax >= x0) {
-                xx = -0.5f * x0 * (fast_log(b0) + fast_log(b1));
-                ok = xx <= xmax;
-            } else {
-                xx = xmax * sqrtf(b0);
-                ok = b1 <= fast_exp(m2ix0 * xx);
-            }
-            const float r = xx * ixmax;
-            const float ct = 1.0f - 2.0f * r * r;
-            if (ok && b2 <= 0.5f * (1.0f + ct * ct)) return ct;
-        } else {
-            float tau, omt;   // tau and 1 - tau, the latter without cancellation
-            if (b0 * (a1 + a2) < a1) {
-                const float e = -a1 * b1;               // in [-ln(1 + 2k), 0]; |e| <= 0.47 for E <= 150 keV
-                omt = one_minus_exp(e);
-                tau = 1.0f - omt;
-            } else {
-                const float t2 = tau0 * tau0 + omt02 * b1;
-                tau = sqrtf(t2);
-                omt = omt02 * (1.0f - b1) * fast_rcp(1.0f + tau);
-            }
-            const float itau = fast_rcp(tau);
-            const float omc = omt * ik * itau;          // 1 - cos(theta)
-            const float ct = 1.0f - omc;
-            const float sin2 = omc * (2.0f - omc);
-            const float g = 1.0f - tau * sin2 * fast_rcp(1.0f + tau * tau);
-            if (b2 <= g) {
-                E *= tau;
-                return ct;
-            }
+    float tau, omt;   // tau and 1 - tau, the latter without cancellation
+    if (b0 * (a1 + a2) < a1) {
+        const float e = -a1 * b1;               // in [-ln(1 + 2k), 0]; |e| <= 0.47 for E <= 150 keV
+        omt = one_minus_exp(e);
+        tau = 1.0f - omt;
+    } else {
+        const float t2 = tau0 * tau0 + omt02 * b1;
+        tau = sqrt_rn(t2);
+        omt = omt02 * (1.0f - b1) * fast_rcp(1.0f + tau);
+    }
+    const float itau = fast_rcp(tau);
+    const float omc = omt * ik * itau;          // 1 - cos(theta)
+    ct = 1.0f - omc;
+    const float sin2 = omc * (2.0f - omc);
+    const float g = 1.0f - tau * sin2 * fast_rcp(1.0f + tau * tau);
+    E *= tau;
+    return b2 <= g;
+}
+
+// A lane's value from another lane of the wavefront (all lanes active).
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, int lane) {
+    return (uint32_t)__builtin_amdgcn_ds_bpermute(lane << 2, (int)v);
+}
+__device__ __forceinline__ float from_lane(float v, int lane) {
+    return __uint_as_float(from_lane(__float_as_uint(v), lane));
+}
+
+// The scattering angles of a wavefront's events (lanes with `scatter`; every
+// lane of the wavefront is active): the first kept try of each, tries counted
+// from 0.  ct, az and the energy after the event go to the event's lane (ct = 1
+// if kMaxTries are rejected).  Try 0 runs in the lane of its event; about a
+// quarter of the events reject it, and the tries after it would run on those
+// few lanes until the last one is kept, 3 to 4 rounds a wavefront.  They are
+// independent (a block each), so the rest is spread over the wavefront: with n
+// events left, groups of 64 / n lanes (rounded down to a power of two) take
+// the next tries of one event at once, and the first kept one of a group counts.
+__device__ __forceinline__ void scatter_angles(bool scatter, bool is_rayleigh, uint32_t pid, uint32_t job,
+                                               uint32_t step, uint32_t k0, uint32_t k1, float x0, float& E,
+                                               float& ct, float& az) {
+    ct = 1.0f;
+    az = 0.0f;
+    bool left = false;
+    if (scatter) {
+        float e = E, c;
+        left = !try_angle(is_rayleigh, pid, job, step, 0u, k0, k1, x0, e, c, az);
+        if (!left) {
+            E = e;
+            ct = c;
         }
     }
-    return 1.0f;
+    uint64_t mask = __ballot(left);
+    const int lane = __lane_id();
+    const uint64_t lt = (1ull << lane) - 1ull;
+    for (uint32_t t0 = 1u; mask && t0 < (uint32_t)kMaxTries;) {
+        const int n = __popcll(mask);
+        const int sh = 31 - __builtin_clz(64 / n);                   // groups of 2^sh lanes
+        const int rank = __popcll(mask & lt);                        // events left in the lanes before this one
+        // event number -> its lane (the lanes without one fill the rest of the permutation)
+        const int by_rank = __builtin_amdgcn_ds_permute((left ? rank : n + lane - rank) << 2, lane);
+        const int g = lane >> sh;
+        const int src = (int)from_lane((uint32_t)by_rank, g);
+        const uint32_t t = t0 + (uint32_t)(lane & ((1 << sh) - 1));
+        // (the event's kind travels in the sign of its energy)
+        const float es = from_lane(is_rayleigh ? -E : E, src);
+        const uint32_t ps = from_lane(pid, src), js = from_lane(job, src), ss = from_lane(step, src);
+        float e = fabsf(es), c = 1.0f, a = 0.0f;
+        const bool ok = g < n && t < (uint32_t)kMaxTries && try_angle(es < 0.0f, ps, js, ss, t, k0, k1, x0, e, c, a);
+        const uint64_t oks = __ballot(ok);
+        const uint64_t mine = (oks >> ((rank << sh) & 63)) & (~0ull >> (64 - (1 << sh)));
+        const int win = ((rank << sh) + (mine ? __builtin_ctzll(mine) : 0)) & 63;
+        const float we = from_lane(e, win), wc = from_lane(c, win), wa = from_lane(a, win);
+        if (left && mine) {
+            E = we;
+            ct = wc;
+            az = wa;
+            left = false;
+        }
+        mask = __ballot(left);
+        t0 += 1u << sh;
+    }
 }
 
 }  // namespace gdrr

@@ -657,24 +657,29 @@ __device__ __forceinline__ void flight_pair_all_local(const KParams& P, const Ta
     }
 }
 
-// A real collision (Sec. 2.4): the ladder value picks Rayleigh, Compton or
+// Real collisions of a wavefront's lanes (Sec. 2.4; every lane is active, those
+// in state kColl have one): the ladder value picks Rayleigh, Compton or
 // photoelectric absorption; scattering samples the angle, updates energy and
 // direction and the distance to the phantom's boundary.
 template <int MODE, bool ALL_LOCAL>
 __device__ __forceinline__ void collide(const KParams& P, const Tables& T, const DVolume& V, int vo, Photon& ph) {
-    const int m = ph.pm;
-    const float* a = P.mu_mass + ((size_t)m * P.n_e + ph.ec.j) * 3;   // j <= n_e - 2
-    const float R = a[0] + ph.ec.f * (a[3] - a[0]);
-    const float C = a[1] + ph.ec.f * (a[4] - a[1]);
-    const float sel = ph.sel;
-    if (!(sel < R + C)) {
-        if (MODE == kModeTrace) trace_out<MODE>(P, ph, kAbsorbed, -1);
-        ph.st = kDead;
-        return;
+    bool scatter = false, is_rayleigh = false;
+    if (ph.st == kColl) {
+        const int m = ph.pm;
+        const float* a = P.mu_mass + ((size_t)m * P.n_e + ph.ec.j) * 3;   // j <= n_e - 2
+        const float R = a[0] + ph.ec.f * (a[3] - a[0]);
+        const float C = a[1] + ph.ec.f * (a[4] - a[1]);
+        const float sel = ph.sel;
+        scatter = sel < R + C;
+        is_rayleigh = sel < R;
+        if (!scatter) {
+            if (MODE == kModeTrace) trace_out<MODE>(P, ph, kAbsorbed, -1);
+            ph.st = kDead;
+        }
     }
-    const bool is_rayleigh = sel < R;
-    float az = 0.0f;
-    const float ct = scatter_angle(is_rayleigh, ph.pid, ph.jid, ph.step, P.k0, P.k1, ph.E, P.x0, az);
+    float ct, az;
+    scatter_angles(scatter, is_rayleigh, ph.pid, ph.jid, ph.step, P.k0, P.k1, P.x0, ph.E, ct, az);
+    if (!scatter) return;
     if (is_rayleigh) {
         ph.nsc += 1u << 16;
     } else {
@@ -827,6 +832,8 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
     ph.pid = 0;
     ph.jid = 0;
     ph.nsc = 0;
+    ph.E = 0.0f;
+    ph.step = 0u;
     ph.sel = 0.0f;
     ph.pair = 0u;
     ph.pm = 0;
@@ -970,7 +977,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
         const int n_coll2 = __popcll(__ballot(ph.st == kColl));
         const int n_fly2 = __popcll(__ballot(ph.st == kFly));
         if (n_coll2 > 0 && (n_coll2 >= P.cdefer || n_fly2 == 0 || w_done || w_hold)) {
-            if (ph.st == kColl) collide<MODE, LOCAL == 3>(P, T, V, vo, ph);
+            collide<MODE, LOCAL == 3>(P, T, V, vo, ph);
         }
     }
 }
