@@ -504,38 +504,47 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     bool any_single = false;
     for (int v = 0; v < B.n_vols; ++v) any_single |= batch_uses(B, v) && B.vols[v].macro <= 0;
     const int n_maj = any_single ? B.n_vols : 0;
-    // local majorants go to LDS (after the tables) while the records of all volumes that the
-    // launch traces fit in kMacroLdsMax (one word per cube in the all-local instantiation)
+    const int n_mat = phys->n_mat;
+    // Local majorants go to LDS (after the tables) while the records of all volumes that the
+    // launch traces fit in kMacroLdsMax.  All-local launches (every traced volume has local
+    // majorants, density is interpolated) keep one word per cube in a grid padded with words that
+    // end a walk (outside_stride); long thin grids, which the padding would more than double, and
+    // tables that leave no room for it take the unpadded 8-byte records, or global memory.
+    // A cube's bound is the same number everywhere, so the tallies do not depend on this.
     int macro_lds[GDRR_MAX_VOLUMES];
     int macro_lds_n = 0;
-    for (int v = 0; v < GDRR_MAX_VOLUMES; ++v) macro_lds[v] = -1;
-    // the all-local instantiation counts a flight's crossings in 9 bits per axis
-    bool small_grids = true;
-    for (int v = 0; v < B.n_vols; ++v)
-        if (B.vols[v].macro > 0 && batch_uses(B, v))
-            small_grids &= cubes(B.vols[v].nx, B.vols[v].macro) <= 512 && cubes(B.vols[v].ny, B.vols[v].macro) <= 512 &&
-                           cubes(B.vols[v].nz, B.vols[v].macro) <= 512;
-    const bool all_local = local && !any_single && interp && small_grids;
-    const size_t rec_bytes = lds_record_bytes(all_local ? 3 : 2);
+    int local_kind = 0;
+    const size_t one_wave = (size_t)(tune.block ? tune.block : 256) / 64;      // least slots of a launch
     if (local) {
-        size_t n = 0;
+        size_t n = 0, padded = 0;
         for (int v = 0; v < B.n_vols; ++v)
-            if (B.vols[v].macro > 0 && batch_uses(B, v))
-                n += (size_t)cubes(B.vols[v].nx, B.vols[v].macro) * cubes(B.vols[v].ny, B.vols[v].macro) *
-                     cubes(B.vols[v].nz, B.vols[v].macro);
-        if (n * rec_bytes <= kMacroLdsMax)
-            for (int v = 0; v < B.n_vols; ++v)
-                if (B.vols[v].macro > 0 && batch_uses(B, v)) {
-                    macro_lds[v] = macro_lds_n;
-                    macro_lds_n += cubes(B.vols[v].nx, B.vols[v].macro) * cubes(B.vols[v].ny, B.vols[v].macro) *
-                                   cubes(B.vols[v].nz, B.vols[v].macro);
-                }
+            if (B.vols[v].macro > 0 && batch_uses(B, v)) {
+                const gdrr_volume& V = B.vols[v];
+                const int cx = cubes(V.nx, V.macro), cy = cubes(V.ny, V.macro), cz = cubes(V.nz, V.macro);
+                n += (size_t)cx * cy * cz;
+                padded += (size_t)outside_stride(cx, cy) * ((size_t)cz + 2);
+            }
+        const auto fits = [&](int kind, size_t records) {
+            return slots_offset_bytes(table_floats2(n_mat, phys->n_e, n_maj) * 8 + records * lds_record_bytes(kind)) +
+                   one_wave * min_slots(kind) * slot_bytes(kind) <= dev.lds_max;
+        };
+        if (n > 0 && !any_single && interp && n * lds_record_bytes(3) <= kMacroLdsMax &&
+            padded * lds_record_bytes(3) <= 2 * kMacroLdsMax && fits(3, padded))
+            local_kind = 3;
+        else if (n > 0 && n * lds_record_bytes(2) <= kMacroLdsMax && fits(2, n))
+            local_kind = 2;
+        else
+            local_kind = 1;
     }
-    const int local_kind = !local ? 0 : (macro_lds_n > 0 ? (all_local ? 3 : 2) : 1);
-    // Rows for the material sets of cubes (all-local launches, at most 8 materials): as many
-    // as keep the workgroups per compute unit that the launch has without them (or the tuned
-    // count), as the runtime's occupancy calculation has it.
-    const int n_mat = phys->n_mat;
+    for (int v = 0; v < GDRR_MAX_VOLUMES; ++v) {
+        macro_lds[v] = -1;
+        if (v >= B.n_vols || local_kind < 2 || B.vols[v].macro <= 0 || !batch_uses(B, v)) continue;
+        const gdrr_volume& V = B.vols[v];
+        const int cx = cubes(V.nx, V.macro), cy = cubes(V.ny, V.macro), cz = cubes(V.nz, V.macro);
+        // (all-local: the offset of cube (0, 0, 0), after the padding below the grid)
+        macro_lds[v] = macro_lds_n + (local_kind == 3 ? outside_stride(cx, cy) : 0);
+        macro_lds_n += local_kind == 3 ? outside_stride(cx, cy) * (cz + 2) : cx * cy * cz;
+    }
     // Default shape.  All-local launches are bound by VALU issue: they gain from early refills
     // and from 1024-thread workgroups, two per compute unit, which share the tables and cube
     // records and so keep 8 wavefronts per SIMD (2e7 photons of a 256x256x160 phantom: 3.44 ms
@@ -551,6 +560,9 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
                                   (size_t)macro_lds_n * lds_record_bytes(local_kind)) +
                (size_t)(block / 64) * n_slots * slot_bytes(local_kind);
     };
+    // Rows for the material sets of cubes (all-local launches, at most 8 materials): as many
+    // as keep the workgroups per compute unit that the launch has without them (or the tuned
+    // count), as the runtime's occupancy calculation has it.
     const void* mfunc = mc_func_for(B.mode, local_kind);
     // (the LDS of a workgroup is allocated in granules of kLdsGranule bytes, which the
     // runtime's occupancy calculation does not round to: the query gets the rounded size)
@@ -743,6 +755,8 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         if (V.macro > 0) {
             d.mnx = cubes(V.nx, V.macro); d.mny = cubes(V.ny, V.macro); d.mnz = cubes(V.nz, V.macro);
             d.mcube = V.macro;
+            d.mlx = (float)(d.mnx - 1); d.mly = (float)(d.mny - 1); d.mlz = (float)(d.mnz - 1);
+            d.msy = d.mnx + 1; d.msz = outside_stride(d.mnx, d.mny);
             d.mex = (float)((double)V.macro * V.dx_mm);
             d.mey = (float)((double)V.macro * V.dy_mm);
             d.mez = (float)((double)V.macro * V.dz_mm);
@@ -784,6 +798,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     kp.e_max = (float)(phys->e0_kev + (double)phys->de_kev * (phys->n_e - 1));
     kp.e_cut = phys->e_cut_kev;
     kp.x0 = phys->rayleigh_x0_invA;
+    kp.mhx0 = -0.5f * phys->rayleigh_x0_invA;
     kp.k0 = (uint32_t)B.seed;
     kp.k1 = (uint32_t)(B.seed >> 32);
     kp.flags = B.flags;

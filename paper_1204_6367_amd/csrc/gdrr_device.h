@@ -127,6 +127,8 @@ struct DVolume {
     // local majorants (null: one majorant per energy interval for the whole volume)
     const uint2* macro;       // per cube: (1 + margin) rho_max (float bits), material bit mask
     int mnx, mny, mnz, mcube; // cubes per axis; voxels per cube edge
+    float mlx, mly, mlz;      // last cube per axis
+    int msy, msz;             // strides of the padded cube grid (all-local launches)
     float mex, mey, mez;      // cube edge, mm
     float imx, imy, imz;      // 1 / cube edge
 };
@@ -204,26 +206,32 @@ __device__ __forceinline__ float box_exit(const DVolume& V, float px, float py, 
 }
 
 // Slab-method entry of the ray S + t d (t >= 0) into the box; false on a miss.
+__device__ __forceinline__ bool slab(float s, float d, float lo, float hi, float& t0, float& t1) {
+    if (d == 0.0f) return !(s < lo || s > hi);
+    const float inv = fast_rcp(d);
+    const float ta = (lo - s) * inv, tb = (hi - s) * inv;
+    t0 = fmaxf(t0, ta > tb ? tb : ta);
+    t1 = fminf(t1, ta > tb ? ta : tb);
+    return true;
+}
+
 __device__ __forceinline__ bool box_entry(const DVolume& V, float sx, float sy, float sz,
                                           float dx, float dy, float dz, float& tin, float& tout) {
-    float t0 = 0.0f, t1 = INFINITY;
-    const float s[3] = {sx, sy, sz}, d[3] = {dx, dy, dz};
-    const float lo[3] = {V.lox, V.loy, V.loz}, hi[3] = {V.hix, V.hiy, V.hiz};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (d[a] == 0.0f) {
-            if (s[a] < lo[a] || s[a] > hi[a]) return false;
-            continue;
-        }
-        const float inv = fast_rcp(d[a]);
-        float ta = (lo[a] - s[a]) * inv, tb = (hi[a] - s[a]) * inv;
-        if (ta > tb) { const float t = ta; ta = tb; tb = t; }
-        t0 = fmaxf(t0, ta);
-        t1 = fminf(t1, tb);
-    }
-    tin = t0;
-    tout = t1;
-    return t0 < t1;
+    tin = 0.0f;
+    tout = INFINITY;
+    const bool in = slab(sx, dx, V.lox, V.hix, tin, tout) && slab(sy, dy, V.loy, V.hiy, tin, tout) &&
+                    slab(sz, dz, V.loz, V.hiz, tin, tout);
+    return in && tin < tout;
+}
+
+// Constants of the Rayleigh form factor, wavefront-uniform: x0, -x0 / 2, -2 / x0.
+struct FormFactor {
+    float x0, mhx0, m2ix0;
+};
+
+// Lanes below this one whose bit is set.
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // One try of the scattering angle of a Compton or a Rayleigh event, both by
@@ -241,22 +249,22 @@ __device__ __forceinline__ bool box_entry(const DVolume& V, float sx, float sy, 
 // the density ~x on [0, 1/lambda] kept with probability exp(-2x/x0); then kept
 // with probability (1 + cos^2)/2.
 __device__ __forceinline__ bool try_angle(bool is_rayleigh, uint32_t pid, uint32_t job, uint32_t step, uint32_t t,
-                                          uint32_t k0, uint32_t k1, float x0, float& E, float& ct, float& az) {
+                                          uint32_t k0, uint32_t k1, const FormFactor& F, float& E, float& ct,
+                                          float& az) {
     const Block b = philox(pid, job, step, 1u + t, k0, k1);
     const float b0 = u24(b.x), b1 = u24(b.y), b2 = u24(b.z);
     az = u24(b.w);
     if (is_rayleigh) {
         const float xmax = E * (1.0f / kHc);
         const float ixmax = kHc * fast_rcp(E);
-        const float m2ix0 = -2.0f * fast_rcp(x0);
         float xx;
         bool ok;
-        if (xmax >= x0) {
-            xx = -0.5f * x0 * (fast_log(b0) + fast_log(b1));
+        if (xmax >= F.x0) {
+            xx = F.mhx0 * (fast_log(b0) + fast_log(b1));
             ok = xx <= xmax;
         } else {
             xx = xmax * sqrt_rn(b0);
-            ok = b1 <= fast_exp(m2ix0 * xx);
+            ok = b1 <= fast_exp(F.m2ix0 * xx);
         }
         const float r = xx * ixmax;
         ct = 1.0f - 2.0f * r * r;
@@ -305,14 +313,14 @@ __device__ __forceinline__ float from_lane(float v, int lane) {
 // events left, groups of 64 / n lanes (rounded down to a power of two) take
 // the next tries of one event at once, and the first kept one of a group counts.
 __device__ __forceinline__ void scatter_angles(bool scatter, bool is_rayleigh, uint32_t pid, uint32_t job,
-                                               uint32_t step, uint32_t k0, uint32_t k1, float x0, float& E,
-                                               float& ct, float& az) {
+                                               uint32_t step, uint32_t k0, uint32_t k1, const FormFactor& F,
+                                               float& E, float& ct, float& az) {
     ct = 1.0f;
     az = 0.0f;
     bool left = false;
     if (scatter) {
         float e = E, c;
-        left = !try_angle(is_rayleigh, pid, job, step, 0u, k0, k1, x0, e, c, az);
+        left = !try_angle(is_rayleigh, pid, job, step, 0u, k0, k1, F, e, c, az);
         if (!left) {
             E = e;
             ct = c;
@@ -320,11 +328,10 @@ __device__ __forceinline__ void scatter_angles(bool scatter, bool is_rayleigh, u
     }
     uint64_t mask = __ballot(left);
     const int lane = __lane_id();
-    const uint64_t lt = (1ull << lane) - 1ull;
     for (uint32_t t0 = 1u; mask && t0 < (uint32_t)kMaxTries;) {
         const int n = __popcll(mask);
         const int sh = 31 - __builtin_clz(64 / n);                   // groups of 2^sh lanes
-        const int rank = __popcll(mask & lt);                        // events left in the lanes before this one
+        const int rank = lanes_below(mask);                        // events left in the lanes before this one
         // event number -> its lane (the lanes without one fill the rest of the permutation)
         const int by_rank = __builtin_amdgcn_ds_permute((left ? rank : n + lane - rank) << 2, lane);
         const int g = lane >> sh;
@@ -334,7 +341,7 @@ __device__ __forceinline__ void scatter_angles(bool scatter, bool is_rayleigh, u
         const float es = from_lane(is_rayleigh ? -E : E, src);
         const uint32_t ps = from_lane(pid, src), js = from_lane(job, src), ss = from_lane(step, src);
         float e = fabsf(es), c = 1.0f, a = 0.0f;
-        const bool ok = g < n && t < (uint32_t)kMaxTries && try_angle(es < 0.0f, ps, js, ss, t, k0, k1, x0, e, c, a);
+        const bool ok = g < n && t < (uint32_t)kMaxTries && try_angle(es < 0.0f, ps, js, ss, t, k0, k1, F, e, c, a);
         const uint64_t oks = __ballot(ok);
         const uint64_t mine = (oks >> ((rank << sh) & 63)) & (~0ull >> (64 - (1 << sh)));
         const int win = ((rank << sh) + (mine ? __builtin_ctzll(mine) : 0)) & 63;
