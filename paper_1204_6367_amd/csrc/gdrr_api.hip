@@ -114,6 +114,7 @@ int cubes(int n, int m) { return (n + m - 1) / m; }
 #define GDRR_MACRO_LDS_MAX (32 << 10)
 #endif
 constexpr size_t kMacroLdsMax = GDRR_MACRO_LDS_MAX;   // bytes of cube records staged in LDS
+constexpr size_t kPaddedLdsMax = 112 << 10;            // the same with the padding of all-local grids
 // LDS allocation granule of a gfx950 workgroup (160 KiB / 128), as measured by
 // calib/lds_granule: three 512-thread workgroups share a compute unit up to 42
 // granules (53760 bytes) each, where hipOccupancyMaxActiveBlocksPerMultiprocessor
@@ -449,16 +450,18 @@ int check_batch(const Batch& B) {
 }
 
 // local: 0 single majorants, 1 local majorants with records in global memory, 2 with records in LDS,
-// 3 every traced volume with local majorants and records in LDS, interpolated density
+// 3 (4) every traced volume with local majorants and records in LDS, interpolated (nearest) density
 template <int MODE>
 const void* mc_func(int local) {
     if constexpr (MODE == kModeBackward)
-        return local == 3 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<3>)
+        return local == 4 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<4>)
+             : local == 3 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<3>)
              : local == 2 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<2>)
              : local == 1 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<1>)
                           : reinterpret_cast<const void*>(&mc_adjoint_kernel<0>);
     else
-        return local == 3 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 3>)
+        return local == 4 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 4>)
+             : local == 3 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 3>)
              : local == 2 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 2>)
              : local == 1 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 1>)
                           : reinterpret_cast<const void*>(&mc_kernel<MODE, 0>);
@@ -507,30 +510,32 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     const int n_mat = phys->n_mat;
     // Local majorants go to LDS (after the tables) while the records of all volumes that the
     // launch traces fit in kMacroLdsMax.  All-local launches (every traced volume has local
-    // majorants, density is interpolated) keep one word per cube in a grid padded with words that
-    // end a walk (outside_stride); long thin grids, which the padding would more than double, and
-    // tables that leave no room for it take the unpadded 8-byte records, or global memory.
-    // A cube's bound is the same number everywhere, so the tallies do not depend on this.
+    // majorants) keep one word per cube in a grid padded with words that
+    // end a walk (outside_stride), at most kPaddedLdsMax bytes (8192 cubes in a grid of one slab
+    // take 105 KB); where tables leave no room for it, or an axis has over 512 cubes, they take
+    // the unpadded 8-byte records, or global memory.  A cube's bound is the same number everywhere.
     int macro_lds[GDRR_MAX_VOLUMES];
     int macro_lds_n = 0;
     int local_kind = 0;
     const size_t one_wave = (size_t)(tune.block ? tune.block : 256) / 64;      // least slots of a launch
     if (local) {
         size_t n = 0, padded = 0;
+        bool small_grids = true;
         for (int v = 0; v < B.n_vols; ++v)
             if (B.vols[v].macro > 0 && batch_uses(B, v)) {
                 const gdrr_volume& V = B.vols[v];
                 const int cx = cubes(V.nx, V.macro), cy = cubes(V.ny, V.macro), cz = cubes(V.nz, V.macro);
                 n += (size_t)cx * cy * cz;
+                small_grids &= cx <= 512 && cy <= 512 && cz <= 512;
                 padded += (size_t)outside_stride(cx, cy) * ((size_t)cz + 2);
             }
         const auto fits = [&](int kind, size_t records) {
             return slots_offset_bytes(table_floats2(n_mat, phys->n_e, n_maj) * 8 + records * lds_record_bytes(kind)) +
                    one_wave * min_slots(kind) * slot_bytes(kind) <= dev.lds_max;
         };
-        if (n > 0 && !any_single && interp && n * lds_record_bytes(3) <= kMacroLdsMax &&
-            padded * lds_record_bytes(3) <= 2 * kMacroLdsMax && fits(3, padded))
-            local_kind = 3;
+        if (n > 0 && !any_single && small_grids && n * lds_record_bytes(3) <= kMacroLdsMax &&
+            padded * lds_record_bytes(3) <= kPaddedLdsMax && fits(3, padded))
+            local_kind = interp ? 3 : 4;
         else if (n > 0 && n * lds_record_bytes(2) <= kMacroLdsMax && fits(2, n))
             local_kind = 2;
         else
@@ -542,8 +547,8 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         const gdrr_volume& V = B.vols[v];
         const int cx = cubes(V.nx, V.macro), cy = cubes(V.ny, V.macro), cz = cubes(V.nz, V.macro);
         // (all-local: the offset of cube (0, 0, 0), after the padding below the grid)
-        macro_lds[v] = macro_lds_n + (local_kind == 3 ? outside_stride(cx, cy) : 0);
-        macro_lds_n += local_kind == 3 ? outside_stride(cx, cy) * (cz + 2) : cx * cy * cz;
+        macro_lds[v] = macro_lds_n + (local_kind >= 3 ? outside_stride(cx, cy) : 0);
+        macro_lds_n += local_kind >= 3 ? outside_stride(cx, cy) * (cz + 2) : cx * cy * cz;
     }
     // Default shape.  All-local launches are bound by VALU issue: they gain from early refills
     // and from 1024-thread workgroups, two per compute unit, which share the tables and cube
@@ -552,7 +557,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // 512x512x256).  A launch with a single-majorant volume waits on its gathers, where late
     // refills do best (512x512x256: 3.21 ms against 3.50).
     // (The trace kernel runs 6 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
-    const bool wide = local_kind == 3 && B.mode != kModeTrace;
+    const bool wide = local_kind >= 3 && B.mode != kModeTrace;
     int block = tune.block ? tune.block : (wide ? 1024 : 256);
     int n_slots = 64;
     const auto lds_for = [&](int rows) {
@@ -572,22 +577,21 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mfunc, block, held));
         return GDRR_OK;
     };
-    // Started photons per wavefront: 64 (a full wavefront starts them), or min_slots() where 64
-    // would not fit the LDS of a workgroup or would cost a workgroup per compute unit (8 against 6
-    // wavefronts per SIMD is worth 5 %, full wavefronts of starts less).
+    // Started photons per wavefront: 64 (a full wavefront starts them), 32 where 64 would not fit
+    // the LDS of a workgroup or would cost a workgroup per compute unit (8 against 6 wavefronts
+    // per SIMD is worth 5 %, full against half wavefronts of starts 3 %), min_slots() where
+    // nothing else fits; workgroups shrink only where that does not fit either.
     {
-        int nb_full = 0, nb_few = 0;
-        const bool fits = lds_for(n_mat) <= dev.lds_max;
-        if (fits && (rc = per_cu_with(lds_for(n_mat), nb_full))) return rc;
-        n_slots = min_slots(local_kind);
+        int nb_64 = 0, nb_32 = 0;
+        if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb_64))) return rc;
+        n_slots = 32;
+        if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb_32))) return rc;
+        if (nb_64 > 0 && (nb_64 >= nb_32 || (tune.blocks_per_cu && tune.blocks_per_cu <= nb_64))) n_slots = 64;
+        else if (nb_32 == 0) n_slots = min_slots(local_kind);
         while (!tune.block && block > 256 && lds_for(n_mat) > dev.lds_max) block /= 2;
-        if (fits) {
-            if ((rc = per_cu_with(lds_for(n_mat), nb_few))) return rc;
-            if (nb_few <= nb_full || (tune.blocks_per_cu && tune.blocks_per_cu <= nb_full)) n_slots = 64;
-        }
     }
     int mask_rows = 0;
-    if (local_kind == 3 && n_mat <= 8 && lds_for(n_mat) <= dev.lds_max) {
+    if (local_kind >= 3 && n_mat <= 8 && lds_for(n_mat) <= dev.lds_max) {
         int target = tune.blocks_per_cu;
         if (!target && (rc = per_cu_with(lds_for(n_mat), target))) return rc;
         const int sets = std::min((1 << n_mat) - 1 - n_mat, (int)kNoRow - n_mat);   // sets of two or more

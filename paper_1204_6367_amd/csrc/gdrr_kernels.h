@@ -71,7 +71,7 @@ __host__ __device__ inline size_t table_floats2(int tot_rows, int n_e, int n_maj
 // Bytes of cube records per cube in LDS: the all-local instantiation keeps one
 // word (the density bound, whose low 5 bits are zero, with a table row there),
 // the others the record as built.
-__host__ __device__ inline size_t lds_record_bytes(int local_kind) { return local_kind == 3 ? 4 : 8; }
+__host__ __device__ inline size_t lds_record_bytes(int local_kind) { return local_kind >= 3 ? 4 : 8; }
 
 // Per wavefront, after the tables and cube records: slots of started photons,
 // from a 16-byte boundary.  A slot is two 16-byte words (position and energy;
@@ -81,8 +81,8 @@ __host__ __device__ inline size_t lds_record_bytes(int local_kind) { return loca
 __host__ __device__ inline size_t slots_offset_bytes(size_t tables_and_records_bytes) {
     return (tables_and_records_bytes + 15) & ~(size_t)15;
 }
-__host__ __device__ inline uint32_t slot_bytes(int local_kind) { return local_kind == 3 ? 32u : 36u; }
-__host__ __device__ inline int min_slots(int local_kind) { return local_kind == 3 ? 32 : 16; }   // (powers of two)
+__host__ __device__ inline uint32_t slot_bytes(int local_kind) { return local_kind >= 3 ? 32u : 36u; }
+__host__ __device__ inline int min_slots(int local_kind) { return local_kind >= 3 ? 32 : 16; }   // (powers of two)
 
 // The row field of an all-local LDS record: 31 = no row (the bound then comes
 // from the cube's material mask in its global record).
@@ -635,17 +635,20 @@ __device__ __forceinline__ bool walk_flight(const KParams& P, const DVolume& V, 
 }
 
 // Both free flights of a pair (words x, y for the first, z, w for the second)
-// in the all-local instantiation.  The walk is set up once: after a null
-// collision the second flight goes on along the same line from the same cube,
-// whose face distances stay valid (re-based to the null collision).  The adjoint
-// sets a walk up for each flight: the walk's state across the collision test
-// and its gradient visit would spill its registers.
-template <int MODE>
+// in the all-local instantiations.  With interpolated density the forward sets
+// the walk up once: after a null collision the second flight goes on along the
+// same line from the same cube, whose face distances stay valid (re-based to
+// the null collision).  The adjoint sets a walk up for each flight: the walk's
+// state across the collision test and its gradient visit would spill its
+// registers.  So does the nearest-voxel lookup, whose flights are those of
+// flight_local to the last bit.
+template <int MODE, bool INTERP>
 __device__ __forceinline__ void flight_pair_all_local(const KParams& P, const Tables& T, const DVolume& V, int vo,
                                                       Photon& ph, const Block& b, const uint32_t* lds_rec,
                                                       bool no_rows) {
+    constexpr bool kOneWalk = INTERP && MODE != kModeBackward;
     Walk w;
-    if constexpr (MODE != kModeBackward) w = walk_setup(V, ph, lds_rec);
+    if constexpr (kOneWalk) w = walk_setup(V, ph, lds_rec);
     const float2* tot = T.tot + ph.ec.j * P.tot_rows;
 #pragma nounroll
     for (int f = 0; f < 2; ++f) {
@@ -655,7 +658,7 @@ __device__ __forceinline__ void flight_pair_all_local(const KParams& P, const Ta
             return;
         }
         ph.step += 1;
-        if constexpr (MODE == kModeBackward) w = walk_setup(V, ph, lds_rec);
+        if constexpr (!kOneWalk) w = walk_setup(V, ph, lds_rec);
         const float tau = -fast_log(u24(f == 0 ? b.x : b.z));
         float t, mb;
         const bool hit = no_rows ? walk_flight<true>(P, V, tot, ph.ec.f, lds_rec, w, tau, t, mb)
@@ -670,13 +673,13 @@ __device__ __forceinline__ void flight_pair_all_local(const KParams& P, const Ta
             return;
         }
         int m;
-        const float rho = cell_density(V, true, ph.px, ph.py, ph.pz, m);
+        const float rho = cell_density(V, INTERP, ph.px, ph.py, ph.pz, m);
         m = m < P.n_mat ? m : P.n_mat - 1;
         const float2 tt = tot[m];
         const float tot_m = tt.x + ph.ec.f * tt.y;
         const float ladder = u24(f == 0 ? b.y : b.w) * mb;
         const bool real = ladder < rho * tot_m;
-        if (MODE == kModeBackward && ph.passb) visit(P, V, true, ph, real, rho, tot_m, mb);
+        if (MODE == kModeBackward && ph.passb) visit(P, V, INTERP, ph, real, rho, tot_m, mb);
         if (real) {
             ph.st = kColl;
             ph.sel = ladder * fast_rcp(rho);
@@ -684,7 +687,7 @@ __device__ __forceinline__ void flight_pair_all_local(const KParams& P, const Ta
             return;
         }
         // a null collision: the second flight starts here, the distances re-based to it
-        if constexpr (MODE != kModeBackward) {
+        if constexpr (kOneWalk) {
             w.tmx -= t;
             w.tmy -= t;
             w.tmz -= t;
@@ -838,10 +841,10 @@ __device__ __forceinline__ bool stage_records_rows(const KParams& P, float2* s_t
 // LOCAL: 0 = every volume has one majorant per energy interval; 1 = some
 // volume tracks with local majorants, cube records read from global memory;
 // 2 = the same with every such volume's records staged in LDS; 3 = every
-// traced volume tracks with local majorants, records in LDS, at most 512 cubes
-// per axis, and density is interpolated (no single-majorant flight and no
-// nearest-voxel lookup in the code at all).  Separate instantiations, so that each loop keeps its
-// register budget.
+// traced volume tracks with local majorants, records in LDS, and density is
+// interpolated (no single-majorant flight in the code at all); 4 = the same
+// with the nearest voxel's density.  Separate instantiations, so that each
+// loop keeps its register budget.
 template <int MODE, int LOCAL>
 __device__ __forceinline__ void mc_body(const KParams& P) {
     extern __shared__ float2 lds[];
@@ -859,7 +862,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
     float4* const slot_d = slot_p + n_slots;
     float* const slot_t = reinterpret_cast<float*>(slot_d + n_slots);
     bool no_rows = false;
-    if (LOCAL == 3) {
+    if (LOCAL >= 3) {
         // (the slots serve as scratch until the transport starts)
         no_rows = stage_records_rows(P, lds, reinterpret_cast<uint32_t*>(lds_rec),
                                      reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lds) + slots_off));
@@ -872,7 +875,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
         }
     }
     __syncthreads();
-    const bool interp = LOCAL == 3 || (P.flags & 1u) != 0;
+    const bool interp = LOCAL == 3 || (LOCAL < 3 && (P.flags & 1u) != 0);
     const int lane = __lane_id();
     const FormFactor F{P.x0, P.mhx0,
                        __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(-2.0f * fast_rcp(P.x0))))};
@@ -967,7 +970,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                         const uint32_t k = pid & (n_slots - 1u);
                         slot_p[k] = make_float4(s.px, s.py, s.pz, s.E);
                         slot_d[k] = make_float4(s.dx, s.dy, s.dz, __int_as_float(s.pix));
-                        if (LOCAL != 3) slot_t[k] = s.trem;
+                        if (LOCAL < 3) slot_t[k] = s.trem;
                     }
                     d_end += nd;
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // the slots are read by other lanes
@@ -982,7 +985,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                     const uint32_t k = ph.pid & (n_slots - 1u);
                     const float4 a = slot_p[k], b = slot_d[k];
                     if (a.w >= 0.0f) {
-                        const Start s{a.x, a.y, a.z, b.x, b.y, b.z, a.w, LOCAL != 3 ? slot_t[k] : 0.0f,
+                        const Start s{a.x, a.y, a.z, b.x, b.y, b.z, a.w, LOCAL < 3 ? slot_t[k] : 0.0f,
                                       __float_as_int(b.w), true};
                         take_start(P, T, P.vol[w_vol].lds_majorant, ph, s);
                         ph.st = kFly;
@@ -1002,9 +1005,9 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
         if (ph.st == kFly) {
             ph.pair += 1u;
             const Block b = philox(ph.pid, ph.jid, ph.pair, 0u, P.k0, P.k1);
-            if constexpr (LOCAL == 3) {
+            if constexpr (LOCAL >= 3) {
                 const uint32_t* lr = reinterpret_cast<const uint32_t*>(lds_rec) + P.macro_lds[w_vol];
-                flight_pair_all_local<MODE>(P, T, V, vo, ph, b, lr, no_rows);
+                flight_pair_all_local<MODE, LOCAL == 3>(P, T, V, vo, ph, b, lr, no_rows);
             } else if (LOCAL == 2 && V.macro) {
                 const uint2* lr = reinterpret_cast<const uint2*>(lds_rec) + P.macro_lds[w_vol];
                 if (flight_local<MODE, 1>(P, T, V, vo, interp, ph, b.x, b.y, lr))
@@ -1023,7 +1026,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
         const int n_coll2 = __popcll(__ballot(ph.st == kColl));
         const int n_fly2 = __popcll(__ballot(ph.st == kFly));
         if (n_coll2 > 0 && (n_coll2 >= P.cdefer || n_fly2 == 0 || w_done || w_hold)) {
-            collide<MODE, LOCAL == 3>(P, T, V, vo, F, ph);
+            collide<MODE, LOCAL >= 3>(P, T, V, vo, F, ph);
         }
     }
 }
@@ -1033,7 +1036,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
 // which the 1024-thread workgroups, two per compute unit, then use.
 template <int MODE, int LOCAL>
 __global__ __launch_bounds__(1024)
-__attribute__((amdgpu_waves_per_eu(MODE == kModeForward && LOCAL == 3 ? 8 : 6))) void mc_kernel(KParams P) {
+__attribute__((amdgpu_waves_per_eu(MODE == kModeForward && LOCAL >= 3 ? 8 : 6))) void mc_kernel(KParams P) {
     mc_body<MODE, LOCAL>(P);
 }
 
@@ -1042,7 +1045,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeForward && LOCAL == 3 ? 8 : 6)))
 // wavefronts per SIMD; it would take 70, and the 44 bytes it spills cost less
 // than the occupancy: 5.38e9 against 5.11e9 histories/s at 6).
 template <int LOCAL>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(LOCAL == 3 ? 8 : 5))) void mc_adjoint_kernel(
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(LOCAL >= 3 ? 8 : 5))) void mc_adjoint_kernel(
     KParams P) {
     mc_body<kModeBackward, LOCAL>(P);
 }
