@@ -109,6 +109,22 @@ int check_volume(const gdrr_volume* v) {
 }
 
 int cubes(int n, int m) { return (n + m - 1) / m; }
+size_t cubes_of(const gdrr_volume& v, int m) {
+    return (size_t)cubes(v.nx, m) * (size_t)cubes(v.ny, m) * (size_t)cubes(v.nz, m);
+}
+
+// The end of the workspace, which the queries count and calls run without too (a call is refused
+// only for want of what its layout needs): the records of the screening cubes of a launch's
+// single-majorant volumes.
+constexpr size_t kScreenCubes = 4096;
+constexpr size_t kExtraBytes = kScreenCubes * sizeof(uint2) + 512;
+
+// The smallest cube edge (2 voxels or more) that cuts the volume into at most `most` cubes.
+int screen_cube_of(const gdrr_volume& v, size_t most) {
+    int m = 2;
+    while (cubes_of(v, m) > most) ++m;
+    return m;
+}
 
 #ifndef GDRR_MACRO_LDS_MAX
 #define GDRR_MACRO_LDS_MAX (32 << 10)
@@ -450,7 +466,9 @@ int check_batch(const Batch& B) {
 }
 
 // local: 0 single majorants, 1 local majorants with records in global memory, 2 with records in LDS,
-// 3 (4) every traced volume with local majorants and records in LDS, interpolated (nearest) density
+// 3 (4) every traced volume with local majorants and records in LDS, interpolated (nearest) density,
+// 5 every traced volume with a single majorant, screened (forward and trace: the adjoint visits null
+// collisions too)
 template <int MODE>
 const void* mc_func(int local) {
     if constexpr (MODE == kModeBackward)
@@ -460,7 +478,8 @@ const void* mc_func(int local) {
              : local == 1 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<1>)
                           : reinterpret_cast<const void*>(&mc_adjoint_kernel<0>);
     else
-        return local == 4 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 4>)
+        return local == 5 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 5>)
+             : local == 4 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 4>)
              : local == 3 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 3>)
              : local == 2 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 2>)
              : local == 1 ? reinterpret_cast<const void*>(&mc_kernel<MODE, 1>)
@@ -493,6 +512,8 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     if ((rc = device_info(dev))) return rc;
     char* wsa = (char*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     const Layout L = carve(wsa, B.vols, phys, B.srcs, B.n_srcs, B.n_jobs, B.n_vols, L0.tally_elems, need_maj);
+    const bool has_extra = ws_bytes >= L.bytes + kExtraBytes;
+    char* const extra = wsa + ((L.bytes + 255) & ~(size_t)255);
     const bool interp = (B.flags & GDRR_INTERP_DENSITY) != 0;
 
     // ---- host tables: jobs, chunk prefix, output offsets ----
@@ -518,6 +539,10 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     int macro_lds_n = 0;
     int local_kind = 0;
     const size_t one_wave = (size_t)(tune.block ? tune.block : 256) / 64;      // least slots of a launch
+    const auto fits = [&](int kind, size_t records) {
+        return slots_offset_bytes(table_floats2(n_mat, phys->n_e, n_maj) * 8 + records * lds_record_bytes(kind)) +
+               one_wave * min_slots(kind) * slot_bytes(kind) <= dev.lds_max;
+    };
     if (local) {
         size_t n = 0, padded = 0;
         bool small_grids = true;
@@ -529,10 +554,6 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
                 small_grids &= cx <= 512 && cy <= 512 && cz <= 512;
                 padded += (size_t)outside_stride(cx, cy) * ((size_t)cz + 2);
             }
-        const auto fits = [&](int kind, size_t records) {
-            return slots_offset_bytes(table_floats2(n_mat, phys->n_e, n_maj) * 8 + records * lds_record_bytes(kind)) +
-                   one_wave * min_slots(kind) * slot_bytes(kind) <= dev.lds_max;
-        };
         if (n > 0 && !any_single && small_grids && n * lds_record_bytes(3) <= kMacroLdsMax &&
             padded * lds_record_bytes(3) <= kPaddedLdsMax && fits(3, padded))
             local_kind = interp ? 3 : 4;
@@ -541,8 +562,29 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         else
             local_kind = 1;
     }
+    // Screening of a single majorant: cubes as small as kScreenCubes in the launch allow (2 voxels at
+    // least), their records after everything else in the workspace; without room there or in LDS,
+    // launches run unscreened.
+    int screen_cube[GDRR_MAX_VOLUMES] = {};
+    uint2* screen_rec[GDRR_MAX_VOLUMES] = {};
+    if (!local && any_single && B.mode != kModeBackward) {
+        int used = 0;
+        for (int v = 0; v < B.n_vols; ++v) used += batch_uses(B, v);
+        size_t n = 0;
+        for (int v = 0; v < B.n_vols; ++v)
+            if (batch_uses(B, v)) {
+                screen_cube[v] = screen_cube_of(B.vols[v], kScreenCubes / used);
+                screen_rec[v] = (uint2*)extra + n;
+                n += cubes_of(B.vols[v], screen_cube[v]);
+            }
+        if (has_extra && fits(5, n)) local_kind = 5;
+    }
     for (int v = 0; v < GDRR_MAX_VOLUMES; ++v) {
         macro_lds[v] = -1;
+        if (local_kind == 5 && v < B.n_vols && screen_cube[v]) {
+            macro_lds[v] = macro_lds_n;
+            macro_lds_n += (int)cubes_of(B.vols[v], screen_cube[v]);
+        }
         if (v >= B.n_vols || local_kind < 2 || B.vols[v].macro <= 0 || !batch_uses(B, v)) continue;
         const gdrr_volume& V = B.vols[v];
         const int cx = cubes(V.nx, V.macro), cy = cubes(V.ny, V.macro), cz = cubes(V.nz, V.macro);
@@ -715,6 +757,12 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         ls.push_back(make_launch((const void*)&cells_kernel,
                                  dim3((unsigned)std::max<size_t>(1, std::min<size_t>((size_t)dev.cus * 16, (nc + 255) / 256))),
                                  dim3(256), 0, cp));
+        if (local_kind == 5) {
+            const int m = screen_cube[v];
+            MacroParams mp{V.density, V.material, V.nx, V.ny, V.nz, m, cubes(V.nx, m), cubes(V.ny, m), cubes(V.nz, m),
+                           phys->n_mat, kScreenScale, 0.0f, screen_rec[v]};
+            ls.push_back(make_launch((const void*)&macro_kernel, dim3((unsigned)cubes_of(V, m)), dim3(256), 0, mp));
+        }
         if (L.macro[v]) {
             MacroParams mp{V.density, V.material, V.nx, V.ny, V.nz, V.macro, cubes(V.nx, V.macro),
                            cubes(V.ny, V.macro), cubes(V.nz, V.macro), phys->n_mat,
@@ -756,17 +804,19 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         d.idx = (float)(1.0 / V.dx_mm); d.idy = (float)(1.0 / V.dy_mm); d.idz = (float)(1.0 / V.dz_mm);
         d.lds_majorant = n_maj ? v * (phys->n_e - 1) : -1;
         d.macro = L.macro[v];
-        if (V.macro > 0) {
-            d.mnx = cubes(V.nx, V.macro); d.mny = cubes(V.ny, V.macro); d.mnz = cubes(V.nz, V.macro);
-            d.mcube = V.macro;
+        const int mc = local_kind == 5 ? screen_cube[v] : V.macro;
+        if (local_kind == 5 && mc > 0) d.screen = screen_rec[v];
+        if (mc > 0) {
+            d.mnx = cubes(V.nx, mc); d.mny = cubes(V.ny, mc); d.mnz = cubes(V.nz, mc);
+            d.mcube = mc;
             d.mlx = (float)(d.mnx - 1); d.mly = (float)(d.mny - 1); d.mlz = (float)(d.mnz - 1);
             d.msy = d.mnx + 1; d.msz = outside_stride(d.mnx, d.mny);
-            d.mex = (float)((double)V.macro * V.dx_mm);
-            d.mey = (float)((double)V.macro * V.dy_mm);
-            d.mez = (float)((double)V.macro * V.dz_mm);
-            d.imx = (float)(1.0 / ((double)V.macro * V.dx_mm));
-            d.imy = (float)(1.0 / ((double)V.macro * V.dy_mm));
-            d.imz = (float)(1.0 / ((double)V.macro * V.dz_mm));
+            d.mex = (float)((double)mc * V.dx_mm);
+            d.mey = (float)((double)mc * V.dy_mm);
+            d.mez = (float)((double)mc * V.dz_mm);
+            d.imx = (float)(1.0 / ((double)mc * V.dx_mm));
+            d.imy = (float)(1.0 / ((double)mc * V.dy_mm));
+            d.imz = (float)(1.0 / ((double)mc * V.dz_mm));
         }
     }
     for (int s = 0; s < B.n_srcs; ++s) {
@@ -850,6 +900,13 @@ size_t batch_bytes(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys
         if (srcs[s].n_spec < 1 || spec_rows(srcs[s]) < 0) return 0;
     return carve(nullptr, vols, phys, srcs, n_srcs, n_jobs, n_vols, tally_elems_of(jobs, n_jobs, srcs), need_maj).bytes +
            256;
+}
+
+// The bytes that the queries return.
+size_t batch_bytes_all(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, const gdrr_source* srcs,
+                       int n_srcs, const gdrr_job* jobs, int n_jobs) {
+    const size_t bytes = batch_bytes(vols, n_vols, phys, srcs, n_srcs, jobs, n_jobs, true);
+    return bytes ? bytes + kExtraBytes : 0;
 }
 
 // --------------------------------------------------------------------------
@@ -1309,7 +1366,7 @@ size_t gdrr_mc_project_workspace(const gdrr_volume* vol, const gdrr_physics* phy
                                  const gdrr_geometry* geom) {
     if (!geom) return 0;
     gdrr_job j = single_job(geom, 0, 0);
-    return batch_bytes(vol, 1, phys, src, 1, &j, 1, true);
+    return batch_bytes_all(vol, 1, phys, src, 1, &j, 1);
 }
 
 int gdrr_mc_project(const gdrr_volume* vol, const gdrr_physics* phys, const gdrr_source* src,
@@ -1349,7 +1406,7 @@ int gdrr_mc_project_static(const gdrr_volume* vol, const gdrr_physics* phys, con
 size_t gdrr_mc_project_batch_workspace(const gdrr_volume* vols, int32_t n_vols, const gdrr_physics* phys,
                                        const gdrr_source* srcs, int32_t n_srcs, const gdrr_job* jobs,
                                        int32_t n_jobs) {
-    return batch_bytes(vols, n_vols, phys, srcs, n_srcs, jobs, n_jobs, true);
+    return batch_bytes_all(vols, n_vols, phys, srcs, n_srcs, jobs, n_jobs);
 }
 
 int gdrr_mc_project_batch(const gdrr_volume* vols, int32_t n_vols, const gdrr_physics* phys,

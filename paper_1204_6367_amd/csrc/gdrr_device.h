@@ -126,6 +126,7 @@ struct DVolume {
     int lds_majorant;         // offset (float2 units) of this volume's majorant table in LDS
     // local majorants (null: one majorant per energy interval for the whole volume)
     const uint2* macro;       // per cube: (1 + margin) rho_max (float bits), material bit mask
+    const uint2* screen;      // screened single majorant: the same of its screening cubes
     int mnx, mny, mnz, mcube; // cubes per axis; voxels per cube edge
     float mlx, mly, mlz;      // last cube per axis
     int msy, msz;             // strides of the padded cube grid (all-local launches)

@@ -73,3 +73,49 @@ def test_padded_grid_walks_as_the_plain_one(gpu, interp):
             assert abs(float(got[:ref.numel()].sum() / ref.sum()) - 1.0) < 1e-3
         else:
             assert torch.equal(got[:ref.numel()], ref), (shape, macro)
+
+
+def project_with(gpu, b, spare, seed, interp, flags=0):
+    """Batch.project on a workspace `spare` bytes smaller than the query's."""
+    import ctypes as C
+    import torch
+    from paper_1204_6367_amd import _abi
+    L = _abi.lib()
+    va, sa, p = b._structs()
+    ws = b.workspace()
+    out = torch.zeros(b.tally_elems, dtype=torch.float64, device="cuda")
+    _abi.check(L.gdrr_mc_project_batch(va, len(b.vols), C.byref(p), sa, len(b.srcs), b._jobs_c, len(b.jobs), None, seed,
+                                       (1 if interp else 0) | 2 | flags, None, out.data_ptr(), ws.data_ptr(),
+                                       ws.numel() - spare, C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    return out
+
+
+EXTRA = 4096 * 8 + 512        # the part of the workspace that calls run without too
+
+
+@pytest.mark.parametrize("interp", [True, False])
+@pytest.mark.parametrize("shape, n_mat", [((1, 1, 1), 1), ((2, 3, 5), 3), ((33, 31, 35), 4), ((17, 64, 40), 9)])
+def test_screened_flights_are_the_plain_ones(gpu, shape, n_mat, interp):
+    """A single majorant screened by cube bounds against
+    the plain flights that a workspace without the extra part gets: bit for
+    bit, with steep densities in one cube, zero, negative, NaN and infinite ones, materials
+    beyond the table, more than eight materials (sets without a row), two volumes."""
+    import torch
+    rng = np.random.default_rng(3)
+    names = [["air", "soft_tissue", "bone", "lung", "aluminium", "water"][k % 6] for k in range(n_mat)]
+    mat = rng.integers(0, n_mat, shape).astype(np.uint8)
+    dens = (10.0 ** rng.uniform(-3.0, 0.5, shape)).astype(np.float32)
+    bad = dens.copy()
+    bad.flat[:: 7] = rng.choice(np.array([0.0, -1.0, np.nan, np.inf], np.float32), bad.flat[:: 7].shape)
+    bad_mat = mat.copy()
+    bad_mat.flat[:: 11] = 250
+    ph = W.Phantom(dens, mat, (200.0 / shape[2], 180.0 / shape[1], 160.0 / shape[0]), names)
+    geom = W.Geometry(nu=30, nv=20, du_mm=8.0, dv_mm=8.0)
+    prob = W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1)
+    vol, phys, src = gpu.upload(prob)
+    vol2 = gpu.DeviceVolume(bad, bad_mat, (9.0, 8.0, 7.0) if max(shape) < 20 else ph.spacing_mm)
+    jobs = [gpu.JobSpec(geom.replace(phi_rad=0.5 * k), 3001 + 17_000 * (k % 2), k, volume=k % 2) for k in range(6)]
+    b = gpu.Batch([vol, vol2], phys, [src], jobs)
+    got, ref = project_with(gpu, b, 0, 4, interp), project_with(gpu, b, EXTRA, 4, interp)
+    assert float(ref.sum()) > 0
+    assert torch.equal(got, ref)
