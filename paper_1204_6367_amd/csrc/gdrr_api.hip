@@ -114,10 +114,11 @@ size_t cubes_of(const gdrr_volume& v, int m) {
 }
 
 // The end of the workspace, which the queries count and calls run without too (a call is refused
-// only for want of what its layout needs): the records of the screening cubes of a launch's
-// single-majorant volumes.
+// only for want of what its layout needs): the chunk dispensers, and the records of the screening
+// cubes of a launch's single-majorant volumes.
+constexpr size_t kDispBytes = (size_t)kDispensers * kDispStride * sizeof(unsigned long long);
 constexpr size_t kScreenCubes = 4096;
-constexpr size_t kExtraBytes = kScreenCubes * sizeof(uint2) + 512;
+constexpr size_t kExtraBytes = kDispBytes + kScreenCubes * sizeof(uint2) + 512;
 
 // The smallest cube edge (2 voxels or more) that cuts the volume into at most `most` cubes.
 int screen_cube_of(const gdrr_volume& v, size_t most) {
@@ -574,7 +575,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         for (int v = 0; v < B.n_vols; ++v)
             if (batch_uses(B, v)) {
                 screen_cube[v] = screen_cube_of(B.vols[v], kScreenCubes / used);
-                screen_rec[v] = (uint2*)extra + n;
+                screen_rec[v] = (uint2*)(extra + kDispBytes) + n;
                 n += cubes_of(B.vols[v], screen_cube[v]);
             }
         if (has_extra && fits(5, n)) local_kind = 5;
@@ -716,6 +717,10 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     const bool resume = B.mode == kModeForward && (B.flags & GDRR_RESUME);
     // ---- clear counters, tallies (unless resuming), the gradient and the majorant scratch ----
     {
+        if (has_extra) {
+            FillParams x{(unsigned long long*)extra, (long long)(kDispBytes / 8)};
+            ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(1), dim3(256), 0, x));
+        }
         FillParams f{L.counter, 8};
         ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(1), dim3(256), 0, f));
         FillParams t{L.tally, (long long)L.tally_elems};
@@ -834,7 +839,8 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     }
     kp.jobs = L.jobs;
     kp.chunk_prefix = L.chunk_prefix;
-    kp.counter = L.counter;
+    kp.counter = has_extra ? (unsigned long long*)extra : L.counter;
+    kp.n_disp = has_extra ? kDispensers : 1;
     kp.tally = L.tally;
     kp.mu_mass = phys->mu_mass;
     kp.response = phys->response;

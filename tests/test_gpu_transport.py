@@ -90,14 +90,14 @@ def project_with(gpu, b, spare, seed, interp, flags=0):
     return out
 
 
-EXTRA = 4096 * 8 + 512        # the part of the workspace that calls run without too
+EXTRA = 8 * 32 * 8 + 4096 * 8 + 512        # the part of the workspace that calls run without too
 
 
 @pytest.mark.parametrize("interp", [True, False])
 @pytest.mark.parametrize("shape, n_mat", [((1, 1, 1), 1), ((2, 3, 5), 3), ((33, 31, 35), 4), ((17, 64, 40), 9)])
 def test_screened_flights_are_the_plain_ones(gpu, shape, n_mat, interp):
-    """A single majorant screened by cube bounds against
-    the plain flights that a workspace without the extra part gets: bit for
+    """A single majorant screened by cube bounds, its chunks from eight dispensers, against
+    the plain flights and one dispenser that a workspace without the extra part gets: bit for
     bit, with steep densities in one cube, zero, negative, NaN and infinite ones, materials
     beyond the table, more than eight materials (sets without a row), two volumes."""
     import torch
