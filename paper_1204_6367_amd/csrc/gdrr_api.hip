@@ -928,7 +928,7 @@ struct RtLayout {
     float* coef[GDRR_MAX_SOURCES];       // [rows][n_spec]
     float* tab[GDRR_MAX_SOURCES];        // [n_spec][n_mat]
     double* inv_wsum[GDRR_MAX_SOURCES];  // [1]
-    CellRec* cells[GDRR_MAX_VOLUMES];    // volumes that some job uses
+    Plane* planes[GDRR_MAX_VOLUMES];    // volumes that some job uses
     size_t bytes;
 };
 
@@ -982,7 +982,8 @@ RtLayout rt_carve(void* ws, const gdrr_volume* vols, int n_vols, const gdrr_phys
         L.inv_wsum[s] = c.take<double>(1);
     }
     for (int v = 0; v < n_vols; ++v)
-        L.cells[v] = volume_used(jobs, n_jobs, v) ? c.take<CellRec>(cell_count(vols[v])) : nullptr;
+        L.planes[v] = volume_used(jobs, n_jobs, v) ? c.take<Plane>(plane_count(vols[v].nx, vols[v].ny, vols[v].nz))
+                                                   : nullptr;
     L.bytes = c.off + 256;
     return L;
 }
@@ -1123,7 +1124,7 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
         DVolume& d = rp.vol[v];
         d.density = V.density;
         d.material = V.material;
-        d.cells = interp ? L.cells[v] : nullptr;
+        rp.planes[v] = interp ? L.planes[v] : nullptr;
         d.cx = V.nx + 1;
         d.cxy = (V.nx + 1) * (V.ny + 1);
         d.nx = V.nx; d.ny = V.ny; d.nz = V.nz; d.nxy = V.nx * V.ny;
@@ -1131,11 +1132,11 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
         d.loy = (float)(-0.5 * V.ny * V.dy_mm); d.hiy = -d.loy;
         d.loz = (float)(-0.5 * V.nz * V.dz_mm); d.hiz = -d.loz;
         d.idx = (float)(1.0 / V.dx_mm); d.idy = (float)(1.0 / V.dy_mm); d.idz = (float)(1.0 / V.dz_mm);
-        if (interp && L.cells[v]) {
-            CellParams cp{V.density, V.material, V.nx, V.ny, V.nz, phys->n_mat, L.cells[v], status};
-            const size_t nc = cell_count(V);
-            ls.push_back(make_launch((const void*)&cells_kernel,
-                                     dim3((unsigned)std::max<size_t>(1, std::min<size_t>((size_t)dev.cus * 16, (nc + 255) / 256))),
+        if (interp && L.planes[v]) {
+            const int tx = (V.nx + 1 + kPlX - 1) / kPlX, tzs = (V.nz + 2 + kPlZ - 1) / kPlZ;
+            PlaneParams cp{V.density, V.material, V.nx, V.ny, V.nz, phys->n_mat, tx, tzs, (V.nz + 2 + tzs - 1) / tzs,
+                           L.planes[v], status};
+            ls.push_back(make_launch((const void*)&planes_kernel, dim3((unsigned)((size_t)tx * tzs * (V.ny + 1))),
                                      dim3(256), 0, cp));
         } else if (volume_used(jobs, n_jobs, v)) {
             const long long nv = (long long)V.nx * V.ny * V.nz;

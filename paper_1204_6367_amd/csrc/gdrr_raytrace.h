@@ -25,7 +25,7 @@
 
 namespace gdrr {
 
-constexpr int kRtBlock = 256;     // 16 x 16 pixels; each wavefront an 8 x 8 quadrant
+constexpr int kRtBlock = 256;     // 16 x 16 pixels; each wavefront 4 detector columns of 16 rows
 constexpr int kXcds = 8;          // workgroup i runs on XCD i mod 8
 
 struct RtSource {
@@ -36,8 +36,32 @@ struct RtSource {
     int n_spec, rows;
 };
 
+// The lattice of voxel centres as the ray tracer reads it: per cell column
+// (i, j), i in [-1, nx-1], j in [-1, ny-1], one 16-byte record per plane of
+// voxel centres, z fastest: the densities of the column's four corners in
+// plane z (clamped into the volume), corner c = bx + 2 by; cell k's corners are
+// planes k and k+1, 32 bytes in a row (planes run from -1 to nz).  The sign
+// bits (densities are >= 0; corner 0's the highest) carry the four corners'
+// common material, or kPlaneLook where they differ or it is that number: the
+// materials are then read from the voxel array.
+//
+// Rays are nearly horizontal and a wavefront holds 4 detector columns of 16
+// rows, so its lanes read runs of z in 4 or so cell columns: about 20 cache
+// lines a step, each used by several lanes at once.  With records of whole
+// cells, x fastest, 8 x 8 lanes of a wavefront whose rays run along x read 64
+// lines a step, and the lines kept for the next steps overflowed L1 and L2.
+// 60 images of 512x512x256 voxels: 12.4 -> 6.6 ms (whole-cell records with z
+// fastest: 6.85, and twice the bytes to build).
+constexpr int kPlaneLook = 15;
+using Plane = __attribute__((ext_vector_type(4))) float;    // (a value in registers: float4's members went to scratch)
+
+__host__ __device__ inline size_t plane_count(int nx, int ny, int nz) {
+    return (size_t)(nx + 1) * (size_t)(ny + 1) * (size_t)(nz + 2);
+}
+
 struct RtParams {
     DVolume vol[GDRR_MAX_VOLUMES];
+    const Plane* planes[GDRR_MAX_VOLUMES];
     RtSource src[GDRR_MAX_SOURCES];
     float dl[GDRR_MAX_VOLUMES];   // interval length per volume, mm
     const DJob* jobs;
@@ -66,6 +90,14 @@ __device__ __forceinline__ void rt_slab(float s, float d, float lo, float hi, fl
     }
 }
 
+// The sign bits of a plane record as a number, the first corner's the highest.
+__device__ __forceinline__ int plane_code(Plane d) {
+    uint32_t c = __float_as_uint(d.x) >> 31;
+    c = __builtin_amdgcn_alignbit(c, __float_as_uint(d.y), 31u);       // (c << 1) | sign
+    c = __builtin_amdgcn_alignbit(c, __float_as_uint(d.z), 31u);
+    return (int)__builtin_amdgcn_alignbit(c, __float_as_uint(d.w), 31u);
+}
+
 __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
     extern __shared__ float rt_lds[];          // [n_mat][kRtBlock]: the lanes' L_m
     // Workgroups are dealt to the XCDs in turn; each XCD walks its own list of
@@ -84,8 +116,8 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
     const unsigned int local = P.unit_first[lo] + (slot - P.unit_pref[lo]);
     const int tiles_u = (J.nu + 15) >> 4;
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int iu = (int)(local % tiles_u) * 16 + (w & 1) * 8 + (l & 7);
-    const int iv = (int)(local / tiles_u) * 16 + (w >> 1) * 8 + (l >> 3);
+    const int iu = (int)(local % tiles_u) * 16 + w * 4 + (l >> 4);
+    const int iv = (int)(local / tiles_u) * 16 + (l & 15);
     if (iu >= J.nu || iv >= J.nv) return;
 
     float* Lm = rt_lds + threadIdx.x;
@@ -107,10 +139,10 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
     if (t0 < t1) {
         const float dl = P.dl[J.vol];
         // the volume's fields in registers for the march
-        const CellRec* __restrict__ cells = V.cells;       // 32-byte records, materials in the sign bits
+        const Plane* __restrict__ planes = P.planes[J.vol];
         const float* __restrict__ dens = V.density;
         const uint8_t* __restrict__ mats = V.material;
-        const int nx = V.nx, ny = V.ny, nz = V.nz, nxy = V.nxy, cx = V.cx, cxy = V.cxy;
+        const int nx = V.nx, ny = V.ny, nz = V.nz, nxy = V.nxy, cx = V.cx, cz = V.nz + 2;
         // the ray in lattice coordinates (voxel units, cell corners at integers):
         // g(t) = g0 + t gd per axis, one FMA per axis and interval
         const float g0x = (J.Sx - V.lox) * V.idx - 0.5f, g0y = (J.Sy - V.loy) * V.idy - 0.5f,
@@ -158,32 +190,46 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
                 acc += h * clean_density(dens[v]);
             }
         } else {
-            // software-pipelined: the next interval's cell record is read while
-            // this one is summed
+            // Software-pipelined: the next interval's corners are read while this one is summed,
+            // unless it lies in the same cell (intervals are half a voxel long: two in five do;
+            // their lanes send no request).
             float h, fx, fy, fz;
             int ix, iy, iz;
             interval(jb, h, fx, fy, fz, ix, iy, iz);
-            const int cell = (iz + 1) * cxy + (iy + 1) * cx + (ix + 1);
-            float4 d0 = *reinterpret_cast<const float4*>(&cells[cell].d[0]);
-            float4 d1 = *reinterpret_cast<const float4*>(&cells[cell].d[4]);
+            // (unsigned: up to 3/2 of 2^31 records)
+            uint32_t cell = (uint32_t)((iy + 1) * cx + (ix + 1)) * (uint32_t)cz + (uint32_t)(iz + 1);
+            Plane d0 = planes[cell], d1 = planes[(size_t)cell + 1];
             for (int j = jb; j < je; ++j) {
                 float hn, fxn, fyn, fzn;
                 int jx, jy, jz;
                 interval(j + 1, hn, fxn, fyn, fzn, jx, jy, jz);
-                const int celln = (jz + 1) * cxy + (jy + 1) * cx + (jx + 1);
-                const float4 n0 = *reinterpret_cast<const float4*>(&cells[celln].d[0]);
-                const float4 n1 = *reinterpret_cast<const float4*>(&cells[celln].d[4]);
+                const uint32_t celln = (uint32_t)((jy + 1) * cx + (jx + 1)) * (uint32_t)cz + (uint32_t)(jz + 1);
+                Plane n0 = d0, n1 = d1;
+                if (celln != cell) {
+                    n0 = planes[celln];
+                    n1 = planes[(size_t)celln + 1];
+                }
+                cell = celln;
                 if (h > 0.0f) {
-                    const uint32_t s0 = __float_as_uint(d0.x), s1 = __float_as_uint(d0.y), s2 = __float_as_uint(d0.z),
-                                   s3 = __float_as_uint(d0.w), s4 = __float_as_uint(d1.x);
+                    const auto corner_material = [&](int c) {
+                        const int x = min(max(ix + (c & 1), 0), nx - 1);
+                        const int y = min(max(iy + ((c >> 1) & 1), 0), ny - 1);
+                        const int z = min(max(iz + (c >> 2), 0), nz - 1);
+                        return min((int)mats[(long long)z * nxy + (long long)y * nx + x], n_mat - 1);
+                    };
                     // the densities without their flag bits
                     const float c0 = fabsf(d0.x), c1 = fabsf(d0.y), c2 = fabsf(d0.z), c3 = fabsf(d0.w);
-                    const float c4 = fabsf(d1.x), c5 = d1.y, c6 = d1.z, c7 = d1.w;
-                    if (!(s0 >> 31)) {
+                    const float c4 = fabsf(d1.x), c5 = fabsf(d1.y), c6 = fabsf(d1.z), c7 = fabsf(d1.w);
+                    const int m = plane_code(d0);
+                    bool one = m == plane_code(d1) && m != kPlaneLook;
+                    if (n_mat > kPlaneLook && m == kPlaneLook && !one) {
+                        one = true;
+                        for (int c = 0; c < 8; ++c) one = one && corner_material(c) == kPlaneLook;
+                    }
+                    if (one) {
                         const float a00 = c0 + fx * (c1 - c0), a01 = c2 + fx * (c3 - c2);
                         const float a10 = c4 + fx * (c5 - c4), a11 = c6 + fx * (c7 - c6);
                         const float b0 = a00 + fy * (a01 - a00), b1 = a10 + fy * (a11 - a10);
-                        const int m = (int)((s1 >> 31) | ((s2 >> 30) & 2u) | ((s3 >> 29) & 4u) | ((s4 >> 28) & 8u));
                         if (m != cur) {
                             if (cur >= 0) Lm[cur * kRtBlock] += acc;
                             cur = m;
@@ -196,12 +242,8 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
                         const float cd[8] = {c0, c1, c2, c3, c4, c5, c6, c7};
 #pragma unroll
                         for (int c = 0; c < 8; ++c) {
-                            const int x = min(max(ix + (c & 1), 0), nx - 1);
-                            const int y = min(max(iy + ((c >> 1) & 1), 0), ny - 1);
-                            const int z = min(max(iz + (c >> 2), 0), nz - 1);
-                            const int m = min((int)mats[(long long)z * nxy + (long long)y * nx + x], n_mat - 1);
                             const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
-                            Lm[m * kRtBlock] += wc * cd[c];
+                            Lm[corner_material(c) * kRtBlock] += wc * cd[c];
                         }
                     }
                 }
@@ -233,7 +275,60 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
     *o = P.accumulate ? *o + val : val;
 }
 
-// Input check of a volume the ray tracer reads without cell records (no
+// Plane records of a volume, by tiles of kPlX cell columns in x by up to kPlZ
+// planes of one cell row: the tile's two voxel rows go through LDS (read with x
+// along the lanes, written with z along the lanes, both contiguous; the odd row
+// length keeps the LDS banks apart).
+constexpr int kPlX = 32, kPlZ = 64;
+
+struct PlaneParams {
+    const float* density;
+    const uint8_t* material;
+    int nx, ny, nz, n_mat;
+    int tiles_x, tiles_z, tz;  // planes per tile (<= kPlZ)
+    Plane* planes;
+    unsigned int* error;       // input-error bits (invalid densities or materials)
+};
+
+__global__ __launch_bounds__(256) void planes_kernel(PlaneParams C) {
+    __shared__ float s_d[2][kPlZ][kPlX + 1];
+    __shared__ uint8_t s_m[2][kPlZ][kPlX + 4];
+    const unsigned int tx = blockIdx.x % (unsigned)C.tiles_x, rest = blockIdx.x / (unsigned)C.tiles_x;
+    const int tz = (int)(rest % (unsigned)C.tiles_z), j = (int)(rest / (unsigned)C.tiles_z) - 1;
+    const int i0 = (int)tx * kPlX - 1;                         // the tile's first cell column
+    const int cols = min(kPlX, C.nx - i0);                     // columns i0 .. i0 + cols - 1 <= nx - 1
+    const int p0 = tz * C.tz, np = min(C.tz, C.nz + 2 - p0);   // planes p0 .. p0 + np - 1
+    unsigned int err = 0u;
+    for (int e = threadIdx.x; e < 2 * np * (cols + 1); e += 256) {
+        const int q = e / (cols + 1), x = e - q * (cols + 1);
+        const int r = q / np, z = q - r * np;
+        const int vx = min(max(i0 + x, 0), C.nx - 1), vy = min(max(j + r, 0), C.ny - 1);
+        const int vz = min(max(p0 + z - 1, 0), C.nz - 1);
+        const size_t v = ((size_t)vz * C.ny + vy) * C.nx + vx;
+        const float rho = C.density[v];
+        const int mr = C.material[v];
+        if (!density_ok(rho)) err |= kErrDensity;
+        if (mr >= C.n_mat) err |= kErrMaterial;
+        s_d[r][z][x] = fabsf(clean_density(rho));              // (-0 loses its sign too)
+        s_m[r][z][x] = (uint8_t)min(mr, C.n_mat - 1);
+    }
+    if (err) atomicOr(C.error, err);
+    __syncthreads();
+    for (int e = threadIdx.x; e < cols * kPlZ; e += 256) {
+        const int x = e / kPlZ, z = e % kPlZ;
+        if (z >= np) continue;
+        const int m0 = s_m[0][z][x], m1 = s_m[0][z][x + 1], m2 = s_m[1][z][x], m3 = s_m[1][z][x + 1];
+        const uint32_t code = m0 == m1 && m0 == m2 && m0 == m3 ? (uint32_t)m0 : (uint32_t)kPlaneLook;
+        Plane d;
+        d.x = __uint_as_float(__float_as_uint(s_d[0][z][x]) | (code & 8u) << 28);
+        d.y = __uint_as_float(__float_as_uint(s_d[0][z][x + 1]) | (code & 4u) << 29);
+        d.z = __uint_as_float(__float_as_uint(s_d[1][z][x]) | (code & 2u) << 30);
+        d.w = __uint_as_float(__float_as_uint(s_d[1][z][x + 1]) | (code & 1u) << 31);
+        C.planes[((size_t)(j + 1) * (C.nx + 1) + (i0 + x + 1)) * (C.nz + 2) + (p0 + z)] = d;
+    }
+}
+
+// Input check of a volume the ray tracer reads without plane records (no
 // interpolation): the status bits of invalid densities and materials.
 struct VolCheckParams {
     const float* density;
