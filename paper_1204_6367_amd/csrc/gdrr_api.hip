@@ -928,7 +928,8 @@ struct RtLayout {
     float* coef[GDRR_MAX_SOURCES];       // [rows][n_spec]
     float* tab[GDRR_MAX_SOURCES];        // [n_spec][n_mat]
     double* inv_wsum[GDRR_MAX_SOURCES];  // [1]
-    Plane* planes[GDRR_MAX_VOLUMES];    // volumes that some job uses
+    Plane* planes[GDRR_MAX_VOLUMES];     // volumes that some job uses
+    uint16_t* codes[GDRR_MAX_VOLUMES];   // (their corners' materials)
     size_t bytes;
 };
 
@@ -982,11 +983,19 @@ RtLayout rt_carve(void* ws, const gdrr_volume* vols, int n_vols, const gdrr_phys
         L.inv_wsum[s] = c.take<double>(1);
     }
     for (int v = 0; v < n_vols; ++v)
-        L.planes[v] = volume_used(jobs, n_jobs, v) ? c.take<Plane>(plane_count(vols[v].nx, vols[v].ny, vols[v].nz))
-                                                   : nullptr;
+        if (volume_used(jobs, n_jobs, v)) {
+            const size_t n = plane_count(vols[v].nx, vols[v].ny, vols[v].nz);
+            L.planes[v] = c.take<Plane>(n);
+            L.codes[v] = c.take<uint16_t>(n);
+        }
     L.bytes = c.off + 256;
     return L;
 }
+
+// Lanes per ray for a number of 16 x 16 tiles.  Measured (us, 1 / 4 / 16 lanes): 192 tiles 330 /
+// 163 / 226, 384 tiles 317 / 222 / 377, 768 tiles 440 / 530 / 970 (256x192 images of 256x256x160
+// voxels); 12 tiles 383 / 149 / 98, 48 tiles 406 / 159 / 139, 96 tiles 419 / 193 / 250 (64x48 images).
+int rt_lanes(unsigned long long tiles) { return tiles <= 64 ? 16 : tiles <= 512 ? 4 : 1; }
 
 constexpr unsigned kRtMaxTiles = (1u << 24) - 1024u;    // grid * block stays below 2^32 work-items
 
@@ -1054,6 +1063,7 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
         tiles += rt_tiles(jobs[k].geom);
         if (tiles > kRtMaxTiles) return fail(GDRR_EINVAL, "too many pixels in one call (2^32 lanes)");
     }
+    const int lanes = rt_lanes(tiles);
     // Units in row-band order: for each phantom, tile row by tile row, that
     // row of every job on the phantom, dealt to the XCDs in turn.  All XCDs
     // then work through the same band of detector rows -- the same slab of
@@ -1125,6 +1135,7 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
         d.density = V.density;
         d.material = V.material;
         rp.planes[v] = interp ? L.planes[v] : nullptr;
+        rp.codes[v] = interp ? L.codes[v] : nullptr;
         d.cx = V.nx + 1;
         d.cxy = (V.nx + 1) * (V.ny + 1);
         d.nx = V.nx; d.ny = V.ny; d.nz = V.nz; d.nxy = V.nx * V.ny;
@@ -1135,7 +1146,7 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
         if (interp && L.planes[v]) {
             const int tx = (V.nx + 1 + kPlX - 1) / kPlX, tzs = (V.nz + 2 + kPlZ - 1) / kPlZ;
             PlaneParams cp{V.density, V.material, V.nx, V.ny, V.nz, phys->n_mat, tx, tzs, (V.nz + 2 + tzs - 1) / tzs,
-                           L.planes[v], status};
+                           L.planes[v], lanes > 1 ? L.codes[v] : nullptr, status};
             ls.push_back(make_launch((const void*)&planes_kernel, dim3((unsigned)((size_t)tx * tzs * (V.ny + 1))),
                                      dim3(256), 0, cp));
         } else if (volume_used(jobs, n_jobs, v)) {
@@ -1163,10 +1174,12 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
     rp.n_mat = phys->n_mat;
     rp.interp = interp ? 1 : 0;
     rp.accumulate = (flags & GDRR_ACCUMULATE) ? 1 : 0;
-    const unsigned long long grid = (unsigned long long)kXcds * most;
+    const unsigned long long grid = (unsigned long long)kXcds * most * lanes;
     if (grid * kRtBlock >= (1ull << 32)) return fail(GDRR_EINVAL, "too many pixels in one call (2^32 lanes)");
     const int timed = (int)ls.size();
-    ls.push_back(make_launch((const void*)&raytrace_kernel, dim3((unsigned)grid), dim3(kRtBlock), lds, rp));
+    const void* const one = phys->n_mat > kPlaneLook ? (const void*)&raytrace_kernel<1, true> : (const void*)&raytrace_kernel<1, false>;
+    ls.push_back(make_launch(lanes == 1 ? one : lanes == 4 ? (const void*)&raytrace_kernel<4, false> : (const void*)&raytrace_kernel<16, false>,
+                             dim3((unsigned)grid), dim3(kRtBlock), lds / lanes, rp));
     TimeEvents* ev = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_time_mu);

@@ -21,6 +21,8 @@
 // material's slot.
 #pragma once
 
+#include <type_traits>
+
 #include "gdrr_device.h"
 
 namespace gdrr {
@@ -53,6 +55,7 @@ struct RtSource {
 // 60 images of 512x512x256 voxels: 12.4 -> 6.6 ms (whole-cell records with z
 // fastest: 6.85, and twice the bytes to build).
 constexpr int kPlaneLook = 15;
+using CodePair = __attribute__((aligned(2))) uint32_t;         // two neighbouring codes
 using Plane = __attribute__((ext_vector_type(4))) float;    // (a value in registers: float4's members went to scratch)
 
 __host__ __device__ inline size_t plane_count(int nx, int ny, int nz) {
@@ -62,6 +65,7 @@ __host__ __device__ inline size_t plane_count(int nx, int ny, int nz) {
 struct RtParams {
     DVolume vol[GDRR_MAX_VOLUMES];
     const Plane* planes[GDRR_MAX_VOLUMES];
+    const uint16_t* codes[GDRR_MAX_VOLUMES];
     RtSource src[GDRR_MAX_SOURCES];
     float dl[GDRR_MAX_VOLUMES];   // interval length per volume, mm
     const DJob* jobs;
@@ -98,16 +102,51 @@ __device__ __forceinline__ int plane_code(Plane d) {
     return (int)__builtin_amdgcn_alignbit(c, __float_as_uint(d.w), 31u);
 }
 
+// A lane's value from lane K of its group of G (DPP: quads by quad_perm, rows of
+// 16 by row_newbcast).
+template <int G, int K>
+__device__ __forceinline__ int group_lane(int v) {
+    if constexpr (G == 1) return v;
+    return __builtin_amdgcn_mov_dpp(v, G == 4 ? K * 0x55 : 0x150 + K, 0xf, 0xf, true);
+}
+template <int G, int K>
+__device__ __forceinline__ float group_lane(float v) {
+    return __int_as_float(group_lane<G, K>(__float_as_int(v)));
+}
+
+// f(integral constant k) for k = 0 .. G - 1.
+template <int G, int K = 0, class F>
+__device__ __forceinline__ void for_group(const F& f) {
+    if constexpr (K < G) {
+        f(std::integral_constant<int, K>{});
+        for_group<G, K + 1>(f);
+    }
+}
+
+// G lanes per ray: lane l of a ray's group reads and interpolates intervals
+// j + l, and the group adds them in their order (every lane the same sums, the
+// ray's LDS slots written by one), so that the image does not depend on G.
+// Many rays take one lane each.  Few rays leave the chip idle, a lone wavefront
+// spending 0.6 us on each of a ray's 560 steps, a third of it in the path of mixed
+// cells, where it waits for the corners' materials one after the other: with G > 1
+// those come along with the corners (codes; with one lane per ray the bytes count,
+// 8.7 against 6.5 ms for 60 images of 512x512x256 voxels), and a mixed cell costs
+// two LDS updates instead of eight.  One 256x192 image of 256x256x160 voxels: 330 ->
+// 160 us at G = 4; one of 64x48 pixels 380 -> 98 us at G = 16.  M16 (G = 1): 16
+// materials, one of them kPlaneLook.
+template <int G, bool M16>
 __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
-    extern __shared__ float rt_lds[];          // [n_mat][kRtBlock]: the lanes' L_m
+    constexpr int kRays = kRtBlock / G;        // rays of the workgroup: 16 / G columns of 16 rows
+    extern __shared__ float rt_lds[];          // [n_mat][kRays]: the rays' L_m
     // Workgroups are dealt to the XCDs in turn; each XCD walks its own list of
     // units in order.  The host orders the units by phantom, then tile row,
     // then job, and deals them round the XCDs, so at any time the whole chip
     // traces one band of detector rows -- one slab of the phantom -- over all
     // that phantom's projections.
-    const unsigned int x = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    if (slot >= P.xcd_tiles[x]) return;         // whole workgroup; no barrier in this kernel
-    int lo = (int)P.xcd_start[x], hi = (int)P.xcd_start[x + 1] - 1;
+    const unsigned int xcd = blockIdx.x % kXcds, in_xcd = blockIdx.x / kXcds;
+    const unsigned int slot = in_xcd / G, part = in_xcd % G;
+    if (slot >= P.xcd_tiles[xcd]) return;       // whole workgroup; no barrier in this kernel
+    int lo = (int)P.xcd_start[xcd], hi = (int)P.xcd_start[xcd + 1] - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (P.unit_pref[mid] <= slot) lo = mid; else hi = mid - 1;
@@ -115,13 +154,14 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
     const DJob& J = P.jobs[P.unit_job[lo]];
     const unsigned int local = P.unit_first[lo] + (slot - P.unit_pref[lo]);
     const int tiles_u = (J.nu + 15) >> 4;
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int iu = (int)(local % tiles_u) * 16 + w * 4 + (l >> 4);
-    const int iv = (int)(local / tiles_u) * 16 + (l & 15);
-    if (iu >= J.nu || iv >= J.nv) return;
+    const int ray = threadIdx.x / G, l = threadIdx.x % G;
+    const int iu = (int)(local % tiles_u) * 16 + (int)part * (16 / G) + (ray >> 4);
+    const int iv = (int)(local / tiles_u) * 16 + (ray & 15);
+    if (iu >= J.nu || iv >= J.nv) return;       // (whole groups)
 
-    float* Lm = rt_lds + threadIdx.x;
-    for (int m = 0; m < P.n_mat; ++m) Lm[m * kRtBlock] = 0.0f;
+    float* Lm = rt_lds + ray;
+    if (l == 0)
+        for (int m = 0; m < P.n_mat; ++m) Lm[m * kRays] = 0.0f;
 
     const DVolume& V = P.vol[J.vol];
     const float uc = ((float)iu + 0.5f - 0.5f * (float)J.nu) * J.du;
@@ -140,135 +180,192 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
         const float dl = P.dl[J.vol];
         // the volume's fields in registers for the march
         const Plane* __restrict__ planes = P.planes[J.vol];
+        const uint16_t* __restrict__ codes = P.codes[J.vol];
         const float* __restrict__ dens = V.density;
         const uint8_t* __restrict__ mats = V.material;
         const int nx = V.nx, ny = V.ny, nz = V.nz, nxy = V.nxy, cx = V.cx, cz = V.nz + 2;
+        const float nx1 = (float)(nx - 1), ny1 = (float)(ny - 1), nz1 = (float)(nz - 1);
         // the ray in lattice coordinates (voxel units, cell corners at integers):
         // g(t) = g0 + t gd per axis, one FMA per axis and interval
         const float g0x = (J.Sx - V.lox) * V.idx - 0.5f, g0y = (J.Sy - V.loy) * V.idy - 0.5f,
                     g0z = (J.Sz - V.loz) * V.idz - 0.5f;
         const float gdx = dx * V.idx, gdy = dy * V.idy, gdz = dz * V.idz;
         const int n_mat = P.n_mat;
-        const bool interp = P.interp != 0;
         float acc = 0.0f;
         int cur = -1;
         // Interval j: its length inside the box h (<= 0 outside the ray's part
         // in the box), the lattice cell (ix, iy, iz) of its midpoint (clamped)
-        // and the fractions there.
-        auto interval = [&](int j, float& h, float& fx, float& fy, float& fz, int& ix, int& iy, int& iz) {
-            const float a = fmaxf((float)j * dl, t0), e = fminf((float)(j + 1) * dl, t1);
+        // and the fractions there.  from: j dl.
+        auto interval = [&](float from, float to, float& h, float& fx, float& fy, float& fz, int& ix, int& iy, int& iz) {
+            const float a = fmaxf(from, t0), e = fminf(to, t1);
             h = e - a;
             const float t = 0.5f * (a + e);
             const float gx = g0x + t * gdx, gy = g0y + t * gdy, gz = g0z + t * gdz;
             const float fx0 = floorf(gx), fy0 = floorf(gy), fz0 = floorf(gz);
-            ix = min(max((int)fx0, -1), nx - 1);
-            iy = min(max((int)fy0, -1), ny - 1);
-            iz = min(max((int)fz0, -1), nz - 1);
+            // (volumes beyond 2^24 voxels along an axis: the clamp still keeps the index inside)
+            ix = min((int)__builtin_amdgcn_fmed3f(fx0, -1.0f, nx1), nx - 1);
+            iy = min((int)__builtin_amdgcn_fmed3f(fy0, -1.0f, ny1), ny - 1);
+            iz = min((int)__builtin_amdgcn_fmed3f(fz0, -1.0f, nz1), nz - 1);
             fx = fminf(fmaxf(gx - fx0, 0.0f), 1.0f);
             fy = fminf(fmaxf(gy - fy0, 0.0f), 1.0f);
             fz = fminf(fmaxf(gz - fz0, 0.0f), 1.0f);
         };
+        // one interval's density-length, in its ray's order: the register sum of the current
+        // material, to its slot when the material changes
+        const auto add_single = [&](int m, float h, float rho) {
+            if (m != cur) {
+                if (cur >= 0 && l == 0) Lm[cur * kRays] += acc;
+                cur = m;
+                acc = 0.0f;
+            }
+            acc += h * rho;
+        };
         // one interval of slack on both sides (rounding of t / dl); empty ones have h <= 0
         const int jb = (int)floorf(t0 / dl) - 1, je = (int)ceilf(t1 / dl) + 1;
-        if (!interp) {
-            for (int j = jb; j < je; ++j) {
+        if (!P.interp) {
+            for (int j0 = jb; j0 < je; j0 += G) {
+                const int j = j0 + l;
                 float h, fx, fy, fz;
                 int ix, iy, iz;
-                interval(j, h, fx, fy, fz, ix, iy, iz);
-                if (!(h > 0.0f)) continue;
+                interval((float)j * dl, (float)(j + 1) * dl, h, fx, fy, fz, ix, iy, iz);
                 // containing voxel: the cell corner nearest to the point
                 const int vx = min(max(ix + (fx >= 0.5f ? 1 : 0), 0), nx - 1);
                 const int vy = min(max(iy + (fy >= 0.5f ? 1 : 0), 0), ny - 1);
                 const int vz = min(max(iz + (fz >= 0.5f ? 1 : 0), 0), nz - 1);
                 const long long v = (long long)vz * nxy + (long long)vy * nx + vx;
-                const int m = min((int)mats[v], n_mat - 1);
-                if (m != cur) {
-                    if (cur >= 0) Lm[cur * kRtBlock] += acc;
-                    cur = m;
-                    acc = 0.0f;
-                }
-                acc += h * clean_density(dens[v]);
+                const int m = h > 0.0f ? min((int)mats[v], n_mat - 1) : -1;
+                const float rho = clean_density(dens[v]);
+                for_group<G>([&](auto k) {
+                    const int mk = group_lane<G, k.value>(m);
+                    const float hk = group_lane<G, k.value>(h), rk = group_lane<G, k.value>(rho);
+                    if (mk >= 0) add_single(mk, hk, rk);
+                });
             }
         } else {
+            // an interval with the corners around its midpoint
+            struct Step {
+                float h, fx, fy, fz;
+                int ix, iy, iz;
+                uint32_t cell;
+                Plane d0, d1;
+                uint32_t cm;                                   // materials of the eight corners, 4 bits each (G > 1)
+            };
+            const auto place = [&](float from, float to, Step& q) {
+                interval(from, to, q.h, q.fx, q.fy, q.fz, q.ix, q.iy, q.iz);
+                // (unsigned: up to 3/2 of 2^31 records)
+                q.cell = (uint32_t)((q.iy + 1) * cx + (q.ix + 1)) * (uint32_t)cz + (uint32_t)(q.iz + 1);
+            };
+            const auto read = [&](Step& q) {
+                q.d0 = planes[q.cell];
+                q.d1 = planes[(size_t)q.cell + 1];
+                if (G > 1) q.cm = *reinterpret_cast<const CodePair*>(codes + q.cell);
+            };
+            const auto add = [&](const Step& q) {
+                const auto corner_material = [&](int c) {
+                    const int x = min(max(q.ix + (c & 1), 0), nx - 1);
+                    const int y = min(max(q.iy + ((c >> 1) & 1), 0), ny - 1);
+                    const int z = min(max(q.iz + (c >> 2), 0), nz - 1);
+                    return min((int)mats[(long long)z * nxy + (long long)y * nx + x], n_mat - 1);
+                };
+                // the densities without their flag bits
+                const float c0 = fabsf(q.d0.x), c1 = fabsf(q.d0.y), c2 = fabsf(q.d0.z), c3 = fabsf(q.d0.w);
+                const float c4 = fabsf(q.d1.x), c5 = fabsf(q.d1.y), c6 = fabsf(q.d1.z), c7 = fabsf(q.d1.w);
+                const float fx = q.fx, fy = q.fy, fz = q.fz;
+                // the cell's material; -1 for several, -2 outside the box
+                int m = plane_code(q.d0);
+                m = m == plane_code(q.d1) && m != kPlaneLook ? m : -1;
+                m = q.h > 0.0f ? m : -2;
+                // (material kPlaneLook itself)
+                if (G > 1) {
+                    if (m == -1 && q.cm == 0x11111111u * (q.cm & 15u)) m = (int)(q.cm & 15u);
+                } else if (M16 && m == -1) {
+                    bool same = true;
+                    for (int c = 0; c < 8; ++c) same = same && corner_material(c) == kPlaneLook;
+                    m = same ? kPlaneLook : -1;
+                }
+                const float a00 = c0 + fx * (c1 - c0), a01 = c2 + fx * (c3 - c2);
+                const float a10 = c4 + fx * (c5 - c4), a11 = c6 + fx * (c7 - c6);
+                const float b0 = a00 + fy * (a01 - a00), b1 = a10 + fy * (a11 - a10);
+                const float rho = b0 + fz * (b1 - b0);
+                for_group<G>([&](auto k) {
+                    const int mk = group_lane<G, k.value>(m);
+                    const float hk = group_lane<G, k.value>(q.h), rk = group_lane<G, k.value>(rho);
+                    if (mk >= 0) {
+                        add_single(mk, hk, rk);
+                    } else if (mk == -1 && l == k.value) {
+                        const float gx0 = 1.0f - fx, gy0 = 1.0f - fy, gz0 = 1.0f - fz;
+                        const float wz0 = q.h * gz0, wz1 = q.h * fz;
+                        const float cd[8] = {c0, c1, c2, c3, c4, c5, c6, c7};
+                        if constexpr (G == 1) {
+#pragma unroll
+                            for (int c = 0; c < 8; ++c) {
+                                const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
+                                Lm[corner_material(c) * kRays] += wc * cd[c];
+                            }
+                        } else {
+                            // Material by material, each one's corners in their order.  left: a bit (the
+                            // highest) in the nibble of every corner still to add.
+                            const uint32_t cm = q.cm;
+                            uint32_t left = 0x88888888u;
+                            do {
+                                const uint32_t mat = (cm >> (__builtin_ctz(left) - 3)) & 15u;
+                                const uint32_t other = cm ^ (0x11111111u * mat);       // nibble 0: this material
+                                float sum = Lm[mat * kRays];
+    #pragma unroll
+                                for (int c = 0; c < 8; ++c) {
+                                    const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
+                                    sum = __builtin_fmaf(wc, other & (15u << (4 * c)) ? 0.0f : cd[c], sum);
+                                }
+                                Lm[mat * kRays] = sum;
+                                left &= ((other & 0x77777777u) + 0x77777777u) | other;
+                            } while (left);
+                        }
+                    }
+                });
+            };
             // Software-pipelined: the next interval's corners are read while this one is summed,
             // unless it lies in the same cell (intervals are half a voxel long: two in five do;
-            // their lanes send no request).
-            float h, fx, fy, fz;
-            int ix, iy, iz;
-            interval(jb, h, fx, fy, fz, ix, iy, iz);
-            // (unsigned: up to 3/2 of 2^31 records)
-            uint32_t cell = (uint32_t)((iy + 1) * cx + (ix + 1)) * (uint32_t)cz + (uint32_t)(iz + 1);
-            Plane d0 = planes[cell], d1 = planes[(size_t)cell + 1];
-            for (int j = jb; j < je; ++j) {
-                float hn, fxn, fyn, fzn;
-                int jx, jy, jz;
-                interval(j + 1, hn, fxn, fyn, fzn, jx, jy, jz);
-                const uint32_t celln = (uint32_t)((jy + 1) * cx + (jx + 1)) * (uint32_t)cz + (uint32_t)(jz + 1);
-                Plane n0 = d0, n1 = d1;
-                if (celln != cell) {
-                    n0 = planes[celln];
-                    n1 = planes[(size_t)celln + 1];
-                }
-                cell = celln;
-                if (h > 0.0f) {
-                    const auto corner_material = [&](int c) {
-                        const int x = min(max(ix + (c & 1), 0), nx - 1);
-                        const int y = min(max(iy + ((c >> 1) & 1), 0), ny - 1);
-                        const int z = min(max(iz + (c >> 2), 0), nz - 1);
-                        return min((int)mats[(long long)z * nxy + (long long)y * nx + x], n_mat - 1);
-                    };
-                    // the densities without their flag bits
-                    const float c0 = fabsf(d0.x), c1 = fabsf(d0.y), c2 = fabsf(d0.z), c3 = fabsf(d0.w);
-                    const float c4 = fabsf(d1.x), c5 = fabsf(d1.y), c6 = fabsf(d1.z), c7 = fabsf(d1.w);
-                    const int m = plane_code(d0);
-                    bool one = m == plane_code(d1) && m != kPlaneLook;
-                    if (n_mat > kPlaneLook && m == kPlaneLook && !one) {
-                        one = true;
-                        for (int c = 0; c < 8; ++c) one = one && corner_material(c) == kPlaneLook;
-                    }
-                    if (one) {
-                        const float a00 = c0 + fx * (c1 - c0), a01 = c2 + fx * (c3 - c2);
-                        const float a10 = c4 + fx * (c5 - c4), a11 = c6 + fx * (c7 - c6);
-                        const float b0 = a00 + fy * (a01 - a00), b1 = a10 + fy * (a11 - a10);
-                        if (m != cur) {
-                            if (cur >= 0) Lm[cur * kRtBlock] += acc;
-                            cur = m;
-                            acc = 0.0f;
-                        }
-                        acc += h * (b0 + fz * (b1 - b0));
-                    } else {
-                        const float gx0 = 1.0f - fx, gy0 = 1.0f - fy, gz0 = 1.0f - fz;
-                        const float wz0 = h * gz0, wz1 = h * fz;
-                        const float cd[8] = {c0, c1, c2, c3, c4, c5, c6, c7};
-#pragma unroll
-                        for (int c = 0; c < 8; ++c) {
-                            const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
-                            Lm[corner_material(c) * kRtBlock] += wc * cd[c];
-                        }
-                    }
-                }
-                h = hn; fx = fxn; fy = fyn; fz = fzn;
-                ix = jx; iy = jy; iz = jz;
-                d0 = n0; d1 = n1;
+            // their lanes send no request).  Reading further ahead gains nothing.
+            float edge = (float)(jb + l + 1) * dl;             // the current interval's end
+            Step q;
+            place((float)(jb + l) * dl, edge, q);
+            read(q);
+            for (int j0 = jb; j0 < je; j0 += G) {
+                Step n;
+                const float from = G == 1 ? edge : (float)(j0 + l + G) * dl;
+                edge = (float)(j0 + l + G + 1) * dl;
+                place(from, edge, n);
+                n.d0 = q.d0;
+                n.d1 = q.d1;
+                if (G > 1) n.cm = q.cm;
+                if (n.cell != q.cell) read(n);
+                add(q);
+                q = n;
             }
         }
-        if (cur >= 0) Lm[cur * kRtBlock] += acc;
+        if (cur >= 0 && l == 0) Lm[cur * kRays] += acc;
     }
 
     float Lr[GDRR_MAX_MATERIALS];
 #pragma unroll
-    for (int m = 0; m < GDRR_MAX_MATERIALS; ++m) Lr[m] = m < P.n_mat ? Lm[m * kRtBlock] : 0.0f;
+    for (int m = 0; m < GDRR_MAX_MATERIALS; ++m) Lr[m] = m < P.n_mat ? Lm[m * kRays] : 0.0f;
     const RtSource& S = P.src[J.src];
     const float* coef = S.coef + (S.rows > 1 ? iu * S.n_spec : 0);
     float sum = 0.0f;
-    for (int k = 0; k < S.n_spec; ++k) {
+    for (int k0 = 0; k0 < S.n_spec; k0 += G) {
+        const int k = G == 1 ? k0 : min(k0 + l, S.n_spec - 1);
         const float* row = S.tab + k * P.n_mat;
         float tau = 0.0f;
 #pragma unroll
         for (int m = 0; m < GDRR_MAX_MATERIALS; ++m)
             if (m < P.n_mat) tau += row[m] * Lr[m];
-        sum += coef[k] * expf(-tau);
+        const float c = coef[k], e = expf(-tau);
+        for_group<G>([&](auto q) {
+            const float cq = group_lane<G, q.value>(c), eq = group_lane<G, q.value>(e);
+            if (G == 1 || k0 + q.value < S.n_spec) sum += cq * eq;
+        });
     }
+    if (l != 0) return;
     const int pix = iv * J.nu + iu;
     const double val = (double)S.fluence[pix] * S.inv_wsum[0] * (double)sum;
     double* o = P.out + P.out_off[J.index] + pix;
@@ -287,6 +384,7 @@ struct PlaneParams {
     int nx, ny, nz, n_mat;
     int tiles_x, tiles_z, tz;  // planes per tile (<= kPlZ)
     Plane* planes;
+    uint16_t* codes;           // the four corners' materials, 4 bits each, or null
     unsigned int* error;       // input-error bits (invalid densities or materials)
 };
 
@@ -324,7 +422,9 @@ __global__ __launch_bounds__(256) void planes_kernel(PlaneParams C) {
         d.y = __uint_as_float(__float_as_uint(s_d[0][z][x + 1]) | (code & 4u) << 29);
         d.z = __uint_as_float(__float_as_uint(s_d[1][z][x]) | (code & 2u) << 30);
         d.w = __uint_as_float(__float_as_uint(s_d[1][z][x + 1]) | (code & 1u) << 31);
-        C.planes[((size_t)(j + 1) * (C.nx + 1) + (i0 + x + 1)) * (C.nz + 2) + (p0 + z)] = d;
+        const size_t at = ((size_t)(j + 1) * (C.nx + 1) + (i0 + x + 1)) * (C.nz + 2) + (p0 + z);
+        C.planes[at] = d;
+        if (C.codes) C.codes[at] = (uint16_t)(m0 | m1 << 4 | m2 << 8 | m3 << 12);
     }
 }
 

@@ -1,0 +1,49 @@
+"""The ray tracer's images do not depend on how many lanes trace a ray."""
+import numpy as np
+import pytest
+
+from paper_1204_6367_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1204_6367_amd import api
+    return api
+
+
+@pytest.mark.parametrize("interp", [True, False])
+@pytest.mark.parametrize("n_mat, shape", [(3, (1, 1, 1)), (4, (21, 30, 33)), (15, (9, 8, 7)), (16, (70, 12, 11))])
+def test_lanes_per_ray(gpu, n_mat, shape, interp):
+    """One, four and sixteen lanes per ray (more than 512, up to 512 and up to 64 tiles in the
+    call) give the same bits: noisy materials (most cells mixed), blocks of one material (the
+    last one's number is the mark of cells to look up), detectors of one pixel to odd tiles,
+    a joint source."""
+    import torch
+    rng = np.random.default_rng(n_mat)
+    names = [["air", "soft_tissue", "bone", "lung", "aluminium", "water"][k % 6] for k in range(n_mat)]
+    mat = rng.integers(0, n_mat, shape).astype(np.uint8)
+    mat[: (shape[0] + 1) // 2] = n_mat - 1
+    dens = rng.uniform(0.0, 2.0, shape).astype(np.float32)
+    dens.flat[:: 5] = rng.choice(np.array([0.0, -0.0, -1.0, np.nan], np.float32), dens.flat[:: 5].shape)
+    ph = W.Phantom(dens, mat, (150.0 / shape[2], 140.0 / shape[1], 130.0 / shape[0]), names)
+    for nu, nv in ((1, 1), (17, 31), (45, 40)):
+        geom = W.Geometry(nu=nu, nv=nv, du_mm=240.0 / nu, dv_mm=200.0 / nv)
+        prob = W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom, joint=nu > 1), geom, 1)
+        vol, phys, src = gpu.upload(prob)
+        tiles = ((nu + 15) // 16) * ((nv + 15) // 16)
+        jobs = [gpu.JobSpec(geom.replace(phi_rad=0.11 * k, theta_rad=0.02 * (k % 3)), 0, k)
+                for k in range(513 // tiles + 1)]
+        many = gpu.Batch([vol], phys, [src], jobs).primary(interp=interp)              # one lane
+        some = gpu.Batch([vol], phys, [src], jobs[: 65 // tiles + 1]).primary(interp=interp)   # four
+        assert 64 < tiles * len(some) <= 512 < tiles * len(many)
+        for k in range(len(some)):
+            assert torch.equal(some[k], many[k]), (nu, k)
+        for k in (0, 7):
+            one = gpu.Batch([vol], phys, [src], [jobs[k]]).primary(interp=interp)      # sixteen
+            assert torch.equal(one[0], many[k]), (nu, k)
+        assert float(sum(m.sum() for m in many)) > 0
