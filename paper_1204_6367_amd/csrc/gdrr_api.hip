@@ -1200,6 +1200,74 @@ size_t dn_buffer_bytes(int n_img, int nv, int nu) {
     return ((size_t)n_img * nv * nu * sizeof(float) + 255) & ~(size_t)255;
 }
 
+// How a stack of images is denoised: tiles of 64 C columns by R rows per wavefront, or whole
+// images in one workgroup each.
+struct DnPlan {
+    const void* kernel;
+    int tiles_u, tiles_v, halo, waves, passes, sweeps;   // a pass takes up to `sweeps`
+    double us;                                           // the estimate that it was chosen by
+};
+
+// The plan is the one that this estimate finds cheapest: a pass takes 2 us and 3e-4 us per
+// pixel that a CU loads and stores, a sweep 0.25 us (barrier and LDS round trip) and 7.5e-5 us
+// per pixel of a CU's regions, halos included.  Fitted to 1 to 60 images of 512 x 384 in each
+// configuration at halos of 8, 16 and 24; it decides between them as measured: one such image,
+// 256 sweeps, halo 16: 182 us with regions of 64 x 56, 216 with 64 x 80, 364 with 128 x 96; 60
+// images, 64 sweeps: 734, 707 and 575 at a halo of 8.
+template <int C, int R>
+void dn_try_tiles(int max_waves, int n_img, int nv, int nu, int iters, bool sel, int cus, DnPlan& best) {
+    const int waves = std::min(max_waves, (nv + R - 1) / R), cols = 64 * C, rows = R * waves;
+    const bool edge = nu < cols || nv < rows;
+    for (const int k : {8, 12, 16, 24}) {
+        if ((nu > cols && 2 * k >= cols) || (nv > rows && 2 * k >= rows)) break;
+        const int du = cols - 2 * k, dv = rows - 2 * k;
+        const int tu = nu <= cols ? 1 : (nu - 2 * k + du - 1) / du, tv = nv <= rows ? 1 : (nv - 2 * k + dv - 1) / dv;
+        const bool one = tu == 1 && tv == 1;
+        const int sweeps = one ? iters : k, passes = one ? 1 : std::max(1, (iters + k - 1) / k);
+        const double px = std::ceil((double)n_img * tu * tv / cus) * cols * rows;
+        const double us = passes * (2.0 + 3e-4 * px) + iters * (0.25 + 7.5e-5 * px);
+        if (!(us < best.us)) continue;
+        best = {edge ? (sel ? (const void*)&denoise_tile_kernel<C, R, 0, true, true> : (const void*)&denoise_tile_kernel<C, R, 0, true, false>)
+                     : (sel ? (const void*)&denoise_tile_kernel<C, R, 0, false, true> : (const void*)&denoise_tile_kernel<C, R, 0, false, false>),
+                tu, tv, k, waves, passes, sweeps, us};
+    }
+}
+
+DnPlan dn_plan_tiles(int n_img, int nv, int nu, int iters, bool sel, int cus) {
+    DnPlan p{};
+    p.us = INFINITY;
+    dn_try_tiles<1, 7>(8, n_img, nv, nu, iters, sel, cus, p);
+    dn_try_tiles<1, 7>(16, n_img, nv, nu, iters, sel, cus, p);
+    dn_try_tiles<1, 5>(16, n_img, nv, nu, iters, sel, cus, p);
+    dn_try_tiles<2, 6>(16, n_img, nv, nu, iters, sel, cus, p);
+    return p;
+}
+
+// Whole images go in rounds of one per CU, with no halo, but a lone one has a single CU; the
+// same estimate, with the cost of a pixel measured for each width (a wavefront's share of the
+// rows costs more moves in narrow ones, and fewer than 4 wavefronts leave SIMDs idle): 90
+// images of 256 x 192, 100 sweeps, 428 us against 409 in tiles, 200 images, 30 sweeps, 155
+// against 152; 360 images, 256 sweeps, 2140 against 3460 or more.
+DnPlan dn_plan_images(int n_img, int nv, int nu, int iters, bool sel, int cus) {
+    DnPlan p{};
+    int rows = 0;
+    if (nu == 256 && nv % 12 == 0) {
+        rows = 12;
+        p.kernel = sel ? (const void*)&denoise_tile_kernel<4, 12, 6, false, true> : (const void*)&denoise_tile_kernel<4, 12, 6, false, false>;
+    } else if (nu == 128 && nv % 24 == 0) {
+        rows = 24;
+        p.kernel = sel ? (const void*)&denoise_tile_kernel<2, 24, 12, false, true> : (const void*)&denoise_tile_kernel<2, 24, 12, false, false>;
+    } else if (nu == 64 && nv % 48 == 0) {
+        rows = 48;
+        p.kernel = sel ? (const void*)&denoise_tile_kernel<1, 48, 24, false, true> : (const void*)&denoise_tile_kernel<1, 48, 24, false, false>;
+    }
+    p.us = INFINITY;
+    if (!rows || nv / rows > kDnMaxWaves) return p;
+    const int waves = nv / rows;
+    const double px = (double)nv * nu, per_px = (rows == 12 ? 8.4e-5 : rows == 24 ? 1.0e-4 : 1.1e-4) * std::max(1.0, 4.0 / waves);
+    return {p.kernel, 1, 1, 0, waves, 1, iters, std::ceil((double)n_img / cus) * (2.0 + 3e-4 * px + iters * (0.25 + per_px * px))};
+}
+
 int run_denoise(const double* shat, long long stride, int n_img, int nv, int nu, float beta, float omega, int iters,
                 float s_floor, double* out, void* ws, size_t ws_bytes, hipStream_t st) {
     if (!shat || !out) return fail(GDRR_EINVAL, "shat / out is NULL");
@@ -1211,8 +1279,7 @@ int run_denoise(const double* shat, long long stride, int n_img, int nv, int nu,
     if (!(omega > 0.0f && omega < 2.0f)) return fail(GDRR_EINVAL, "omega must be in (0, 2)");
     if (iters < 0 || iters > (1 << 20)) return fail(GDRR_EINVAL, "iters must be in [0, 2^20]");
     if (!(s_floor > 0.0f) || !std::isfinite(s_floor)) return fail(GDRR_EINVAL, "s_floor must be finite and > 0");
-    const int tiles_u = (nu + kDnTileU - 1) / kDnTileU, tiles_v = (nv + kDnTileV - 1) / kDnTileV;
-    if ((long long)n_img * tiles_u * tiles_v >= (1ll << 31)) return fail(GDRR_EINVAL, "too many tiles in one call");
+    if ((long long)n_img * ((nu + 47) / 48) * ((nv + 63) / 64) >= (1ll << 31)) return fail(GDRR_EINVAL, "too many tiles in one call");
     const size_t in_bytes = ((size_t)(n_img - 1) * (size_t)stride + (size_t)npix) * sizeof(double);
     const size_t out_bytes = (size_t)n_img * (size_t)npix * sizeof(double);
     if (ranges_overlap(shat, in_bytes, out, out_bytes)) return fail(GDRR_EINVAL, "out must not overlap shat");
@@ -1220,51 +1287,38 @@ int run_denoise(const double* shat, long long stride, int n_img, int nv, int nu,
     if (!ws || ws_bytes < 2 * buf + 256) return fail(GDRR_EINVAL, "workspace too small: need " + std::to_string(2 * buf + 256) + " bytes");
     char* wsa = (char*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     float* pp[2] = {(float*)wsa, (float*)(wsa + buf)};
+    // Shat as float32, kept by the first pass for the others (counted by the query; without it
+    // every pass reads the doubles)
+    float* const hf = ws_bytes >= 3 * buf + 256 ? (float*)(wsa + 2 * buf) : nullptr;
+    DevInfo dev;
+    int rc;
+    if ((rc = device_info(dev))) return rc;
+    const bool sel = s_floor < 1.17549435e-38f;            // (the least normal number)
+    DnPlan plan = dn_plan_tiles(n_img, nv, nu, iters, sel, dev.cus);
+    if (const DnPlan whole = dn_plan_images(n_img, nv, nu, iters, sel, dev.cus); whole.us < plan.us) plan = whole;
+    if ((long long)n_img * plan.tiles_u * plan.tiles_v >= (1ll << 31)) return fail(GDRR_EINVAL, "too many tiles in one call");
     std::vector<Launch> ls;
-    // whole images in one workgroup's registers: 64 C columns, R rows per wavefront
-    const void* image_kernel = nullptr;
-    int image_waves = 0;
-    const int img_c[3] = {4, 2, 1}, img_r[3] = {12, 24, 48};
-    const void* img_k[3] = {(const void*)&denoise_image_kernel<4, 12>, (const void*)&denoise_image_kernel<2, 24>,
-                            (const void*)&denoise_image_kernel<1, 48>};
-    for (int q = 0; q < 3 && !image_kernel; ++q)
-        if (nu == 64 * img_c[q] && nv % img_r[q] == 0 && nv / img_r[q] <= 16) {
-            image_kernel = img_k[q];
-            image_waves = nv / img_r[q];
-        }
-    const int passes = image_kernel ? 0 : std::max(1, (iters + kDnHalo - 1) / kDnHalo);
-    if (image_kernel) {
-        DnParams d{};
-        d.shat = shat;
-        d.shat_stride = stride;
-        d.out = out;
-        d.n_img = n_img; d.nv = nv; d.nu = nu;
-        d.iters = iters;
-        d.omega = omega;
-        d.inv_beta = 1.0f / beta;
-        d.s_floor = s_floor;
-        ls.push_back(make_launch(image_kernel, dim3((unsigned)n_img), dim3(64 * image_waves), 0, d));
-    }
-    for (int p = 0; p < passes; ++p) {
-        DnParams d{};
-        d.shat = shat;
-        d.shat_stride = stride;
+    DnParams d{};
+    d.shat = shat;
+    d.shat_stride = stride;
+    d.n_img = n_img; d.nv = nv; d.nu = nu;
+    d.omega = omega;
+    d.inv_beta = 1.0f / beta;
+    d.s_floor = s_floor;
+    d.tiles_u = plan.tiles_u; d.tiles_v = plan.tiles_v; d.halo = plan.halo;
+    for (int p = 0; p < plan.passes; ++p) {
+        const bool last = p + 1 == plan.passes;
+        d.h_in = p > 0 ? hf : nullptr;
+        d.h_out = p == 0 && !last ? hf : nullptr;
         d.s_in = p == 0 ? nullptr : pp[p & 1];
-        d.s_out = p + 1 == passes ? nullptr : pp[(p + 1) & 1];
-        d.out = p + 1 == passes ? out : nullptr;
-        d.n_img = n_img; d.nv = nv; d.nu = nu; d.tiles_u = tiles_u; d.tiles_v = tiles_v;
-        d.iters = std::min(kDnHalo, iters - p * kDnHalo);
-        d.omega = omega;
-        d.inv_beta = 1.0f / beta;
-        d.s_floor = s_floor;
-        const bool inside = nv >= kDnWaves * kDnRows && nu >= kDnCols;
-        ls.push_back(make_launch(inside ? (const void*)&denoise_inside_kernel : (const void*)&denoise_kernel,
-                                 dim3((unsigned)(n_img * tiles_u * tiles_v)), dim3(kDnBlock), 0, d));
+        d.s_out = last ? nullptr : pp[(p + 1) & 1];
+        d.out = last ? out : nullptr;
+        d.iters = std::min(plan.sweeps, iters - p * plan.sweeps);
+        ls.push_back(make_launch(plan.kernel, dim3((unsigned)(n_img * plan.tiles_u * plan.tiles_v)), dim3(64 * plan.waves), 0, d));
     }
     TimeEvents* ev = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_time_mu);
-        int rc;
         if (g_timing && (rc = timing_events(&ev))) return rc;
     }
     return run_direct(ls, st, ev ? 0 : -1, ev, ev ? (int)ls.size() - 1 : -1);
@@ -1475,7 +1529,7 @@ int gdrr_primary(const gdrr_volume* vols, int32_t n_vols, const gdrr_physics* ph
 
 size_t gdrr_denoise_workspace(int32_t n_img, int32_t nv, int32_t nu) {
     if (n_img < 1 || nv < 1 || nu < 1) return 0;
-    return 2 * dn_buffer_bytes(n_img, nv, nu) + 256;
+    return 3 * dn_buffer_bytes(n_img, nv, nu) + 256;
 }
 
 int gdrr_denoise(const double* shat, int64_t shat_stride, int32_t n_img, int32_t nv, int32_t nu, float beta,
