@@ -385,6 +385,27 @@ size_t tally_elems_of(const gdrr_job* jobs, int n_jobs, const gdrr_source* srcs)
     return e;
 }
 
+// A pass over a volume: its cell records (if cells is not null) and the maxima of its densities.
+Launch voxels_launch(const gdrr_volume& V, int n_mat, bool interp, int cus, CellRec* cells, bool maxima,
+                     unsigned int* rho_max, unsigned int* present, unsigned int* status) {
+    const size_t blocks = ((size_t)(V.nx + 1) * (size_t)(V.ny + 1) + 255) / 256;
+    // 2 cells in z per workgroup, so that the workgroups in flight write a few planes and not
+    // columns all over the records (512 x 512 x 256: 560 us; 4 cells 619, 8 cells 648, 65 cells
+    // 692); 4 with the maxima, which every workgroup has to hand in (64^3, no records: 8.7 us
+    // against 10.9 with 2); more where the grid's 65535 in y would not do
+    const int planes = std::max(maxima ? 4 : 2, (int)(((size_t)V.nz + 65535) / 65535));
+    const VoxelParams p{V.density, V.material, V.nx, V.ny, V.nz, n_mat, planes, cells, status, rho_max, present};
+    const void* const f = !cells  ? (interp ? (const void*)&voxels_kernel<false, 2> : (const void*)&voxels_kernel<false, 1>)
+                          : !maxima ? (const void*)&voxels_kernel<true, 0>
+                          : interp  ? (const void*)&voxels_kernel<true, 2>
+                                    : (const void*)&voxels_kernel<true, 1>;
+    return make_launch(f, dim3((unsigned)blocks, (unsigned)((V.nz + planes) / planes)), dim3(256), 0, p);
+}
+
+// Lanes per cube of the local majorants: the large cubes of large volumes are few (13 x 13 x 7 of
+// 40^3 voxels: 1183 workgroups, 118 us with 1024 lanes, 315 with 256).
+unsigned macro_block(int cube) { return cube > 12 ? 1024u : 256u; }
+
 struct Batch {
     const gdrr_volume* vols;
     int n_vols;
@@ -736,47 +757,36 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         FillParams p{(unsigned long long*)L.present, (long long)B.n_vols * 128};
         ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(4), dim3(256), 0, p));
     }
-    // ---- majorants ----
-    const float* maj = B.majorants;
-    if (need_maj) {
-        for (int v = 0; v < B.n_vols; ++v) {
-            const gdrr_volume& V = B.vols[v];
-            MajParams m{V.density, V.material, V.nx, V.ny, V.nz, interp ? 1 : 0, phys->n_mat, L.rho_max + 256 * v,
-                        L.present + 256 * v, status};
-            const long long nvox = (long long)V.nx * V.ny * V.nz;
-            const unsigned g = (unsigned)std::max<long long>(1, std::min<long long>(dev.cus * 8, (nvox + 255) / 256));
-            ls.push_back(make_launch((const void*)&rho_max_kernel, dim3(g), dim3(256), 0, m));
+    // ---- cell records of every volume that has photons; the maxima for the majorants, if they
+    // are not the caller's and any volume is tracked by one (all volumes are checked then) ----
+    for (int v = 0; v < B.n_vols; ++v) {
+        const bool cells = batch_uses(B, v);
+        if (!cells && !need_maj) continue;
+        const gdrr_volume& V = B.vols[v];
+        ls.push_back(voxels_launch(V, phys->n_mat, interp, dev.cus, cells ? L.cells[v] : nullptr, need_maj && (n_maj || !cells),
+                                   L.rho_max + 256 * v, L.present + 256 * v, status));
+        if (need_maj && n_maj) {
             MajFinParams fp{L.rho_max + 256 * v, L.present + 256 * v, phys->mu_mass, phys->n_mat, phys->n_e,
                             1.0 + (double)(1.0f / 1048576.0f), L.majorants + (size_t)v * (phys->n_e - 1),
                             status};
             ls.push_back(make_launch((const void*)&majorant_kernel, dim3((phys->n_e + 254) / 256), dim3(256), 0, fp));
         }
-        maj = L.majorants;
-    }
-    // ---- cell records of every volume that has photons ----
-    for (int v = 0; v < B.n_vols; ++v) {
-        if (!batch_uses(B, v)) continue;
-        const gdrr_volume& V = B.vols[v];
-        CellParams cp{V.density, V.material, V.nx, V.ny, V.nz, phys->n_mat, L.cells[v], status};
-        const size_t nc = cell_count(V);
-        ls.push_back(make_launch((const void*)&cells_kernel,
-                                 dim3((unsigned)std::max<size_t>(1, std::min<size_t>((size_t)dev.cus * 16, (nc + 255) / 256))),
-                                 dim3(256), 0, cp));
+        if (!cells) continue;
         if (local_kind == 5) {
             const int m = screen_cube[v];
             MacroParams mp{V.density, V.material, V.nx, V.ny, V.nz, m, cubes(V.nx, m), cubes(V.ny, m), cubes(V.nz, m),
                            phys->n_mat, kScreenScale, 0.0f, screen_rec[v]};
-            ls.push_back(make_launch((const void*)&macro_kernel, dim3((unsigned)cubes_of(V, m)), dim3(256), 0, mp));
+            ls.push_back(make_launch((const void*)&macro_kernel, dim3((unsigned)cubes_of(V, m)), dim3(macro_block(m)), 0, mp));
         }
         if (L.macro[v]) {
             MacroParams mp{V.density, V.material, V.nx, V.ny, V.nz, V.macro, cubes(V.nx, V.macro),
                            cubes(V.ny, V.macro), cubes(V.nz, V.macro), phys->n_mat,
                            1.0 + (double)V.macro_margin, V.macro_rho_min, L.macro[v]};
             const size_t nm = (size_t)mp.mnx * mp.mny * mp.mnz;
-            // one workgroup of 256 per cube
+            // one workgroup per cube
             ls.push_back(make_launch((const void*)&macro_kernel,
                                      dim3((unsigned)std::max<size_t>(1, std::min<size_t>((size_t)dev.cus * 16, nm))),
-                                     dim3(256), 0, mp));
+                                     dim3(macro_block(V.macro)), 0, mp));
         }
     }
     // ---- sources: CDFs and guide tables ----
@@ -844,7 +854,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     kp.tally = L.tally;
     kp.mu_mass = phys->mu_mass;
     kp.response = phys->response;
-    kp.majorants = maj;
+    kp.majorants = need_maj ? L.majorants : B.majorants;
     kp.total_chunks = chunks;
     kp.n_jobs = B.n_jobs;
     kp.n_vols = B.n_vols;
@@ -1426,11 +1436,7 @@ int gdrr_majorant(const gdrr_volume* vol, const gdrr_physics* phys, uint32_t fla
     std::vector<Launch> ls;
     FillParams f{head, 8 + 256};
     ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(2), dim3(256), 0, f));
-    MajParams m{vol->density, vol->material, vol->nx, vol->ny, vol->nz, (flags & GDRR_INTERP_DENSITY) ? 1 : 0,
-                phys->n_mat, rmax, pres, err};
-    const long long nvox = (long long)vol->nx * vol->ny * vol->nz;
-    const unsigned g = (unsigned)std::max<long long>(1, std::min<long long>(dev.cus * 8, (nvox + 255) / 256));
-    ls.push_back(make_launch((const void*)&rho_max_kernel, dim3(g), dim3(256), 0, m));
+    ls.push_back(voxels_launch(*vol, phys->n_mat, (flags & GDRR_INTERP_DENSITY) != 0, dev.cus, nullptr, true, rmax, pres, err));
     MajFinParams fp{rmax, pres, phys->mu_mass, phys->n_mat, phys->n_e, 1.0 + (double)margin, out, err};
     ls.push_back(make_launch((const void*)&majorant_kernel, dim3((phys->n_e + 254) / 256), dim3(256), 0, fp));
     return run_direct(ls, st);
