@@ -794,13 +794,14 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         const gdrr_source& S = B.srcs[s];
         const SrcArea& A = L.src[s];
         const int rows = spec_rows(S);
-        SrcPrepParams sp{S.spec_prob, S.n_spec, rows, A.spec_cdf, A.spec_guide, (int)A.spec_k, status};
-        ls.push_back(make_launch((const void*)&cdf_kernel, dim3(rows), dim3(1024), 0, sp));
-        const unsigned gk = (unsigned)std::min<size_t>((size_t)dev.cus * 8, ((size_t)rows * A.spec_k + 255) / 256);
-        ls.push_back(make_launch((const void*)&guide_kernel, dim3(gk), dim3(256), 0, sp));
-        SrcPrepParams fp{S.fluence, S.fu * S.fv, 1, A.flu_cdf, A.flu_guide, (int)A.flu_k, status};
-        ls.push_back(make_launch((const void*)&cdf_kernel, dim3(1), dim3(1024), 0, fp));
-        ls.push_back(make_launch((const void*)&guide_kernel, dim3((A.flu_k + 255) / 256), dim3(256), 0, fp));
+        const CdfTable flu{S.fluence, S.fu * S.fv, 1, A.flu_cdf, A.flu_guide, (int)A.flu_k};
+        const SrcPrepParams sp{{{S.spec_prob, S.n_spec, rows, A.spec_cdf, A.spec_guide, (int)A.spec_k}, flu}, status};
+        const bool is_long = flu.n > kLongTable;
+        const unsigned blocks = is_long ? kSegs / kSegBlock : 1;
+        ls.push_back(make_launch((const void*)&cdf_kernel, dim3(rows + blocks), dim3(kSegs), 0, sp));
+        if (!is_long) continue;
+        ls.push_back(make_launch((const void*)&long_cdf_kernel, dim3(blocks), dim3(kSegs), 0, LongCdfParams{flu, status}));
+        ls.push_back(make_launch((const void*)&guide_kernel, dim3((A.flu_k + 255) / 256), dim3(256), 0, flu));
     }
     // ---- the persistent transport kernel ----
     KParams kp{};
@@ -1172,7 +1173,7 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
         RtPrepParams pp{S.spec_e_kev, S.spec_prob, S.fluence, S.n_spec, S.fu * S.fv, phys->mu_mass, phys->response,
                         phys->n_mat, phys->n_e, (double)phys->e0_kev, (double)phys->de_kev, L.coef[s], L.tab[s],
                         L.inv_wsum[s], status};
-        ls.push_back(make_launch((const void*)&raytrace_prep_kernel, dim3(spec_rows(S)), dim3(256), 0, pp));
+        ls.push_back(make_launch((const void*)&raytrace_prep_kernel, dim3(spec_rows(S) + 1), dim3(kRtPrepBlock), 0, pp));
         rp.src[s] = RtSource{S.fluence, L.coef[s], L.tab[s], L.inv_wsum[s], S.n_spec, spec_rows(S)};
     }
     rp.jobs = L.jobs;

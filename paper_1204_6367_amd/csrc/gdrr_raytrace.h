@@ -449,7 +449,8 @@ __global__ __launch_bounds__(256) void volume_check_kernel(VolCheckParams C) {
 
 // Per source: the channel weights phi_k r(E_k) / sum phi (workgroup r: row r
 // of a joint source), the table 0.1 mu_tot(m, E_k) (linear in E between grid
-// points) and 1 / sum w (workgroup 0).
+// points; workgroup 0) and 1 / sum w (the last workgroup, one CU's loads: 16 in
+// flight per lane: 256 x 192 weights 6.6 us, was 56 with 256 lanes and one load each).
 struct RtPrepParams {
     const float* spec_e;
     const float* spec_p;          // [rows][n_spec]
@@ -465,39 +466,47 @@ struct RtPrepParams {
     unsigned int* error;          // input-error bits (invalid spectrum or fluence weights)
 };
 
-__global__ __launch_bounds__(256) void raytrace_prep_kernel(RtPrepParams R) {
-    __shared__ double red[2][256];
+constexpr int kRtPrepBlock = 1024;
+
+__global__ __launch_bounds__(kRtPrepBlock) void raytrace_prep_kernel(RtPrepParams R) {
+    __shared__ double red[kRtPrepBlock];
     const int row = blockIdx.x;
-    const float* phi = R.spec_p + (size_t)row * R.n_spec;
-    float* coef = R.coef + (size_t)row * R.n_spec;
-    double sp = 0.0, sw = 0.0;
+    const bool fluence = row + 1 == (int)gridDim.x;
+    const float* phi = fluence ? R.fluence : R.spec_p + (size_t)row * R.n_spec;
+    const int n = fluence ? R.npix : R.n_spec;
+    double sum = 0.0;
     bool bad = false;
-    for (int k = threadIdx.x; k < R.n_spec; k += 256) {
+    int k = threadIdx.x;
+    for (; k + 15 * kRtPrepBlock < n; k += 16 * kRtPrepBlock) {    // 16 loads in flight
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = phi[k + u * kRtPrepBlock];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const double x = (double)v[u];
+            bad = bad || !(x >= 0.0) || isinf(x);
+            sum += x;
+        }
+    }
+    for (; k < n; k += kRtPrepBlock) {
         const double x = (double)phi[k];
         bad = bad || !(x >= 0.0) || isinf(x);
-        sp += x;
+        sum += x;
     }
-    if (row == 0)
-        for (int k = threadIdx.x; k < R.npix; k += 256) {
-            const double x = (double)R.fluence[k];
-            bad = bad || !(x >= 0.0) || isinf(x);
-            sw += x;
-        }
-    if (bad) atomicOr(R.error, kErrWeights);
-    red[0][threadIdx.x] = sp;
-    red[1][threadIdx.x] = sw;
+    red[threadIdx.x] = sum;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + s];
-            red[1][threadIdx.x] += red[1][threadIdx.x + s];
-        }
+    for (int s = kRtPrepBlock / 2; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    const double psum = red[0][0], wsum = red[1][0];
-    if (row == 0 && threadIdx.x == 0) R.inv_wsum[0] = wsum > 0.0 ? 1.0 / wsum : 0.0;
-    if (threadIdx.x == 0 && (!(psum > 0.0) || (row == 0 && !(wsum > 0.0)))) atomicOr(R.error, kErrWeights);
-    for (int k = threadIdx.x; k < R.n_spec; k += 256) {
+    const double psum = red[0];
+    if (bad || (threadIdx.x == 0 && !(psum > 0.0))) atomicOr(R.error, kErrWeights);
+    if (fluence) {
+        if (threadIdx.x == 0) R.inv_wsum[0] = psum > 0.0 ? 1.0 / psum : 0.0;
+        return;
+    }
+    float* coef = R.coef + (size_t)row * R.n_spec;
+    for (int k = threadIdx.x; k < R.n_spec; k += kRtPrepBlock) {
         const double E = (double)R.spec_e[k];
         const double g = (E - R.e0) / R.de;
         int j = (int)floor(g);
