@@ -385,6 +385,38 @@ size_t tally_elems_of(const gdrr_job* jobs, int n_jobs, const gdrr_source* srcs)
     return e;
 }
 
+// The tables that a call's host code makes for its kernels, with the gaps that the workspace
+// leaves between them: one copy, or none where they fit a kernel's arguments.
+struct TableImage {
+    char* dev;                                 // the first table
+    std::vector<char>& host;
+    TableImage(void* first, void* end, std::vector<char>& staging) : dev((char*)first), host(staging) {
+        host.assign(((size_t)((char*)end - dev) + 3) & ~(size_t)3, 0);
+    }
+    void put(const void* table, const void* src, size_t bytes) { std::memcpy(host.data() + ((const char*)table - dev), src, bytes); }
+};
+
+// Clears `fills` and writes the tables (by the kernel if they fit its arguments and by_kernel
+// says so: a cached graph's kernels keep their arguments).
+int add_setup(std::vector<Launch>& ls, const std::vector<FillParams>& fills, const TableImage& t, bool by_kernel, hipStream_t st) {
+    SetupParams p{};
+    size_t most = 1;
+    for (const FillParams& f : fills) {
+        if (f.n <= 0) continue;
+        p.f[p.fills++] = f;
+        most = std::max(most, (size_t)f.n);
+    }
+    by_kernel = by_kernel && t.host.size() <= sizeof(p.image);
+    if (by_kernel) {
+        p.tables = (uint32_t*)t.dev;
+        p.words = (int)(t.host.size() / 4);
+        std::memcpy(p.image, t.host.data(), t.host.size());
+    }
+    ls.push_back(make_launch((const void*)&setup_kernel, dim3((unsigned)std::min<size_t>(4096, (most + 255) / 256)), dim3(256), 0, p));
+    if (!by_kernel) GDRR_HIP(hipMemcpyAsync(t.dev, t.host.data(), t.host.size(), hipMemcpyHostToDevice, st));
+    return GDRR_OK;
+}
+
 // A pass over a volume: its cell records (if cells is not null) and the maxima of its densities.
 Launch voxels_launch(const gdrr_volume& V, int n_mat, bool interp, int cus, CellRec* cells, bool maxima,
                      unsigned int* rho_max, unsigned int* present, unsigned int* status) {
@@ -689,7 +721,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     const int cdefer = tune.coll_defer ? tune.coll_defer : (wide && !tune.defer ? 12 : defer);
 
     const size_t n_jobs = (size_t)B.n_jobs;
-    const size_t job_bytes = sizeof(unsigned long long) * (n_jobs + 1);
+    const size_t job_bytes = sizeof(unsigned long long) * (n_jobs + 1);       // of the chunk prefix
     std::vector<unsigned long long> prefix(n_jobs + 1);
     std::vector<DJob> dj(n_jobs);
     std::vector<long long> out_off(n_jobs);
@@ -718,44 +750,29 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // The volume order of the dispenser: jobs are taken in array order; a
     // wavefront drains before it changes phantom, so callers group jobs by volume.
     std::vector<Launch> ls;
-    if (B.tables_by_kernel) {
-        if (n_jobs != 1) return fail(GDRR_EINVAL, "internal: kernel-written tables need one job");
-        JobTableParams jt{L.chunk_prefix, L.jobs, L.out_off, prefix[0], prefix[1], out_off[0], dj[0]};
-        ls.push_back(make_launch((const void*)&job_table_kernel, dim3(1), dim3(64), 0, jt));
-    } else {
-        g_staging.resize(job_bytes + sizeof(DJob) * n_jobs + sizeof(long long) * n_jobs + 1024);
-        char* hs = g_staging.data();
-        std::memcpy(hs, prefix.data(), job_bytes);
-        GDRR_HIP(hipMemcpyAsync(L.chunk_prefix, hs, job_bytes, hipMemcpyHostToDevice, st));
-        std::memcpy(hs + job_bytes, dj.data(), sizeof(DJob) * n_jobs);
-        GDRR_HIP(hipMemcpyAsync(L.jobs, hs + job_bytes, sizeof(DJob) * n_jobs, hipMemcpyHostToDevice, st));
-        std::memcpy(hs + job_bytes + sizeof(DJob) * n_jobs, out_off.data(), sizeof(long long) * n_jobs);
-        GDRR_HIP(hipMemcpyAsync(L.out_off, hs + job_bytes + sizeof(DJob) * n_jobs, sizeof(long long) * n_jobs,
-                                hipMemcpyHostToDevice, st));
-    }
+    TableImage tables(L.chunk_prefix, L.out_off + n_jobs, g_staging);
+    tables.put(L.chunk_prefix, prefix.data(), job_bytes);
+    tables.put(L.jobs, dj.data(), sizeof(DJob) * n_jobs);
+    tables.put(L.out_off, out_off.data(), sizeof(long long) * n_jobs);
+    if (B.tables_by_kernel && tables.host.size() > sizeof(SetupParams::image))
+        return fail(GDRR_EINVAL, "internal: the tables do not fit a kernel's arguments");
 
     unsigned int* status = (unsigned int*)(L.counter + 1);    // input-error bits of this call
     const bool resume = B.mode == kModeForward && (B.flags & GDRR_RESUME);
     // ---- clear counters, tallies (unless resuming), the gradient and the majorant scratch ----
     {
-        if (has_extra) {
-            FillParams x{(unsigned long long*)extra, (long long)(kDispBytes / 8)};
-            ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(1), dim3(256), 0, x));
-        }
-        FillParams f{L.counter, 8};
-        ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(1), dim3(256), 0, f));
-        FillParams t{L.tally, (long long)L.tally_elems};
-        if (!resume)
-            ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(std::max<unsigned>(1, std::min<size_t>(4096, (L.tally_elems + 255) / 256))), dim3(256), 0, t));
+        std::vector<FillParams> fills = {{L.counter, 8}};
+        if (has_extra) fills.push_back({(unsigned long long*)extra, (long long)(kDispBytes / 8)});
+        if (!resume) fills.push_back({L.tally, (long long)L.tally_elems});
         if (B.mode == kModeBackward && !(B.flags & GDRR_ACCUMULATE)) {
             const gdrr_volume& V = B.vols[B.only_volume];
-            GradClearParams g{B.grad, (long long)V.nx * V.ny * V.nz};
-            ls.push_back(make_launch((const void*)&grad_zero_kernel, dim3(1024), dim3(256), 0, g));
+            fills.push_back({(unsigned long long*)B.grad, (long long)V.nx * V.ny * V.nz});       // (the bits of 0.0)
         }
-        FillParams r{(unsigned long long*)L.rho_max, (long long)B.n_vols * 128};   // 256 u32 per volume
-        ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(4), dim3(256), 0, r));
-        FillParams p{(unsigned long long*)L.present, (long long)B.n_vols * 128};
-        ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(4), dim3(256), 0, p));
+        if (need_maj) {
+            fills.push_back({(unsigned long long*)L.rho_max, (long long)B.n_vols * 128});   // 256 u32 per volume
+            fills.push_back({(unsigned long long*)L.present, (long long)B.n_vols * 128});
+        }
+        if ((rc = add_setup(ls, fills, tables, !B.use_graph, st))) return rc;
     }
     // ---- cell records of every volume that has photons; the maxima for the majorants, if they
     // are not the caller's and any volume is tracked by one (all volumes are checked then) ----
@@ -1120,26 +1137,17 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
     }
     rp.xcd_start[kXcds] = (unsigned int)ujob.size();
     const size_t nu_ = ujob.size();
-    const size_t b_jobs = sizeof(DJob) * nj, b_u = sizeof(unsigned int) * nu_, b_off = sizeof(long long) * nj;
-    g_staging.resize(b_jobs + 3 * b_u + b_off);
-    char* hs = g_staging.data();
-    std::memcpy(hs, dj.data(), b_jobs);
-    std::memcpy(hs + b_jobs, ujob.data(), b_u);
-    std::memcpy(hs + b_jobs + b_u, ufirst.data(), b_u);
-    std::memcpy(hs + b_jobs + 2 * b_u, upref.data(), b_u);
-    std::memcpy(hs + b_jobs + 3 * b_u, off.data(), b_off);
-    GDRR_HIP(hipMemcpyAsync(L.jobs, hs, b_jobs, hipMemcpyHostToDevice, st));
-    GDRR_HIP(hipMemcpyAsync(L.unit_job, hs + b_jobs, b_u, hipMemcpyHostToDevice, st));
-    GDRR_HIP(hipMemcpyAsync(L.unit_first, hs + b_jobs + b_u, b_u, hipMemcpyHostToDevice, st));
-    GDRR_HIP(hipMemcpyAsync(L.unit_pref, hs + b_jobs + 2 * b_u, b_u, hipMemcpyHostToDevice, st));
-    GDRR_HIP(hipMemcpyAsync(L.out_off, hs + b_jobs + 3 * b_u, b_off, hipMemcpyHostToDevice, st));
+    const size_t b_u = sizeof(unsigned int) * nu_;
+    TableImage tables(L.jobs, L.out_off + nj, g_staging);
+    tables.put(L.jobs, dj.data(), sizeof(DJob) * nj);
+    tables.put(L.unit_job, ujob.data(), b_u);
+    tables.put(L.unit_first, ufirst.data(), b_u);
+    tables.put(L.unit_pref, upref.data(), b_u);
+    tables.put(L.out_off, off.data(), sizeof(long long) * nj);
 
     std::vector<Launch> ls;
     unsigned int* status = (unsigned int*)(L.head + 1);
-    {
-        FillParams f{L.head, 8};
-        ls.push_back(make_launch((const void*)&fill_zero_kernel, dim3(1), dim3(256), 0, f));
-    }
+    if ((rc = add_setup(ls, {{L.head, 8}}, tables, true, st))) return rc;
     for (int v = 0; v < n_vols; ++v) {
         const gdrr_volume& V = vols[v];
         DVolume& d = rp.vol[v];
