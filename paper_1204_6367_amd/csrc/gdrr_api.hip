@@ -983,6 +983,14 @@ unsigned long long rt_run_length(const gdrr_job* jobs, int n_jobs) {
     return std::min(widest, std::max<unsigned long long>(4, total / (8ull * kXcds)));
 }
 
+template <bool SMALL>
+const void* rt_kernel(int lanes, int n_mat) {
+    return lanes == 4    ? (const void*)&raytrace_kernel<4, false, SMALL>
+           : lanes == 16 ? (const void*)&raytrace_kernel<16, false, SMALL>
+           : n_mat > kPlaneLook ? (const void*)&raytrace_kernel<1, true, SMALL>
+                                : (const void*)&raytrace_kernel<1, false, SMALL>;
+}
+
 unsigned long long rt_row_units(const gdrr_geometry& g, unsigned long long run) {
     return (unsigned long long)((g.nv + 15) / 16) * (((unsigned long long)((g.nu + 15) / 16) + run - 1) / run);
 }
@@ -1148,8 +1156,10 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
     std::vector<Launch> ls;
     unsigned int* status = (unsigned int*)(L.head + 1);
     if ((rc = add_setup(ls, {{L.head, 8}}, tables, true, st))) return rc;
+    bool small = true;                         // every index and stride of the plane records below 2^24
     for (int v = 0; v < n_vols; ++v) {
         const gdrr_volume& V = vols[v];
+        small = small && std::max(std::max((long long)V.nx, (long long)V.ny), (long long)(V.nx + 1) * (V.nz + 2)) < (1ll << 24) - 1;
         DVolume& d = rp.vol[v];
         d.density = V.density;
         d.material = V.material;
@@ -1196,9 +1206,8 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
     const unsigned long long grid = (unsigned long long)kXcds * most * lanes;
     if (grid * kRtBlock >= (1ull << 32)) return fail(GDRR_EINVAL, "too many pixels in one call (2^32 lanes)");
     const int timed = (int)ls.size();
-    const void* const one = phys->n_mat > kPlaneLook ? (const void*)&raytrace_kernel<1, true> : (const void*)&raytrace_kernel<1, false>;
-    ls.push_back(make_launch(lanes == 1 ? one : lanes == 4 ? (const void*)&raytrace_kernel<4, false> : (const void*)&raytrace_kernel<16, false>,
-                             dim3((unsigned)grid), dim3(kRtBlock), lds / lanes, rp));
+    const void* const f = small ? rt_kernel<true>(lanes, phys->n_mat) : rt_kernel<false>(lanes, phys->n_mat);
+    ls.push_back(make_launch(f, dim3((unsigned)grid), dim3(kRtBlock), lds / lanes, rp));
     TimeEvents* ev = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_time_mu);

@@ -43,9 +43,9 @@ struct RtSource {
 // voxel centres, z fastest: the densities of the column's four corners in
 // plane z (clamped into the volume), corner c = bx + 2 by; cell k's corners are
 // planes k and k+1, 32 bytes in a row (planes run from -1 to nz).  The sign
-// bits (densities are >= 0; corner 0's the highest) carry the four corners'
-// common material, or kPlaneLook where they differ or it is that number: the
-// materials are then read from the voxel array.
+// bits (densities are >= 0; corner 0's the highest) of plane k carry the common
+// material of cell k's eight corners, or kPlaneLook where they differ or it is that
+// number: the materials are then read from the voxel array.
 //
 // Rays are nearly horizontal and a wavefront holds 4 detector columns of 16
 // rows, so its lanes read runs of z in 4 or so cell columns: about 20 cache
@@ -102,6 +102,10 @@ __device__ __forceinline__ int plane_code(Plane d) {
     return (int)__builtin_amdgcn_alignbit(c, __float_as_uint(d.w), 31u);
 }
 
+// a b for a, b < 2^24 (the low 32 bits; one instruction with an addition, where the
+// full product takes four times as long).
+__device__ __forceinline__ uint32_t mul_u24(uint32_t a, uint32_t b) { return (a & 0xFFFFFFu) * (b & 0xFFFFFFu); }
+
 // A lane's value from lane K of its group of G (DPP: quads by quad_perm, rows of
 // 16 by row_newbcast).
 template <int G, int K>
@@ -133,8 +137,12 @@ __device__ __forceinline__ void for_group(const F& f) {
 // 8.7 against 6.5 ms for 60 images of 512x512x256 voxels), and a mixed cell costs
 // two LDS updates instead of eight.  One 256x192 image of 256x256x160 voxels: 330 ->
 // 160 us at G = 4; one of 64x48 pixels 380 -> 98 us at G = 16.  M16 (G = 1): 16
-// materials, one of them kPlaneLook.
-template <int G, bool M16>
+// materials, one of them kPlaneLook.  SMALL: no index of the plane records or their
+// rows' stride reaches 2^24, so a cell's number takes two 24-bit products (full ones cost
+// four instructions each) and floats hold every bound; with the material in the lower
+// plane's record alone, 8 of 75 instructions an interval: 64 images of 256x192 of 256x256x160
+// voxels 2980 -> 2807 us, 60 of 512x512x256 (bound by the records' 4.8 TB/s) 6480 -> 6400.
+template <int G, bool M16, bool SMALL>
 __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
     constexpr int kRays = kRtBlock / G;        // rays of the workgroup: 16 / G columns of 16 rows
     extern __shared__ float rt_lds[];          // [n_mat][kRays]: the rays' L_m
@@ -184,6 +192,7 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
         const float* __restrict__ dens = V.density;
         const uint8_t* __restrict__ mats = V.material;
         const int nx = V.nx, ny = V.ny, nz = V.nz, nxy = V.nxy, cx = V.cx, cz = V.nz + 2;
+        const uint32_t row = (uint32_t)cx * (uint32_t)cz;
         const float nx1 = (float)(nx - 1), ny1 = (float)(ny - 1), nz1 = (float)(nz - 1);
         // the ray in lattice coordinates (voxel units, cell corners at integers):
         // g(t) = g0 + t gd per axis, one FMA per axis and interval
@@ -203,9 +212,14 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
             const float gx = g0x + t * gdx, gy = g0y + t * gdy, gz = g0z + t * gdz;
             const float fx0 = floorf(gx), fy0 = floorf(gy), fz0 = floorf(gz);
             // (volumes beyond 2^24 voxels along an axis: the clamp still keeps the index inside)
-            ix = min((int)__builtin_amdgcn_fmed3f(fx0, -1.0f, nx1), nx - 1);
-            iy = min((int)__builtin_amdgcn_fmed3f(fy0, -1.0f, ny1), ny - 1);
-            iz = min((int)__builtin_amdgcn_fmed3f(fz0, -1.0f, nz1), nz - 1);
+            ix = (int)__builtin_amdgcn_fmed3f(fx0, -1.0f, nx1);
+            iy = (int)__builtin_amdgcn_fmed3f(fy0, -1.0f, ny1);
+            iz = (int)__builtin_amdgcn_fmed3f(fz0, -1.0f, nz1);
+            if (!SMALL) {
+                ix = min(ix, nx - 1);
+                iy = min(iy, ny - 1);
+                iz = min(iz, nz - 1);
+            }
             fx = fminf(fmaxf(gx - fx0, 0.0f), 1.0f);
             fy = fminf(fmaxf(gy - fy0, 0.0f), 1.0f);
             fz = fminf(fmaxf(gz - fz0, 0.0f), 1.0f);
@@ -253,7 +267,10 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
             const auto place = [&](float from, float to, Step& q) {
                 interval(from, to, q.h, q.fx, q.fy, q.fz, q.ix, q.iy, q.iz);
                 // (unsigned: up to 3/2 of 2^31 records)
-                q.cell = (uint32_t)((q.iy + 1) * cx + (q.ix + 1)) * (uint32_t)cz + (uint32_t)(q.iz + 1);
+                if (SMALL)
+                    q.cell = mul_u24((uint32_t)(q.iy + 1), row) + mul_u24((uint32_t)(q.ix + 1), (uint32_t)cz) + (uint32_t)(q.iz + 1);
+                else
+                    q.cell = (uint32_t)((q.iy + 1) * cx + (q.ix + 1)) * (uint32_t)cz + (uint32_t)(q.iz + 1);
             };
             const auto read = [&](Step& q) {
                 q.d0 = planes[q.cell];
@@ -273,7 +290,7 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
                 const float fx = q.fx, fy = q.fy, fz = q.fz;
                 // the cell's material; -1 for several, -2 outside the box
                 int m = plane_code(q.d0);
-                m = m == plane_code(q.d1) && m != kPlaneLook ? m : -1;
+                m = m != kPlaneLook ? m : -1;
                 m = q.h > 0.0f ? m : -2;
                 // (material kPlaneLook itself)
                 if (G > 1) {
@@ -389,17 +406,17 @@ struct PlaneParams {
 };
 
 __global__ __launch_bounds__(256) void planes_kernel(PlaneParams C) {
-    __shared__ float s_d[2][kPlZ][kPlX + 1];
-    __shared__ uint8_t s_m[2][kPlZ][kPlX + 4];
+    __shared__ float s_d[2][kPlZ + 1][kPlX + 1];
+    __shared__ uint8_t s_m[2][kPlZ + 1][kPlX + 4];
     const unsigned int tx = blockIdx.x % (unsigned)C.tiles_x, rest = blockIdx.x / (unsigned)C.tiles_x;
     const int tz = (int)(rest % (unsigned)C.tiles_z), j = (int)(rest / (unsigned)C.tiles_z) - 1;
     const int i0 = (int)tx * kPlX - 1;                         // the tile's first cell column
     const int cols = min(kPlX, C.nx - i0);                     // columns i0 .. i0 + cols - 1 <= nx - 1
     const int p0 = tz * C.tz, np = min(C.tz, C.nz + 2 - p0);   // planes p0 .. p0 + np - 1
     unsigned int err = 0u;
-    for (int e = threadIdx.x; e < 2 * np * (cols + 1); e += 256) {
+    for (int e = threadIdx.x; e < 2 * (np + 1) * (cols + 1); e += 256) {        // (and the plane above the tile)
         const int q = e / (cols + 1), x = e - q * (cols + 1);
-        const int r = q / np, z = q - r * np;
+        const int r = q / (np + 1), z = q - r * (np + 1);
         const int vx = min(max(i0 + x, 0), C.nx - 1), vy = min(max(j + r, 0), C.ny - 1);
         const int vz = min(max(p0 + z - 1, 0), C.nz - 1);
         const size_t v = ((size_t)vz * C.ny + vy) * C.nx + vx;
@@ -416,14 +433,16 @@ __global__ __launch_bounds__(256) void planes_kernel(PlaneParams C) {
         const int x = e / kPlZ, z = e % kPlZ;
         if (z >= np) continue;
         const int m0 = s_m[0][z][x], m1 = s_m[0][z][x + 1], m2 = s_m[1][z][x], m3 = s_m[1][z][x + 1];
-        const uint32_t code = m0 == m1 && m0 == m2 && m0 == m3 ? (uint32_t)m0 : (uint32_t)kPlaneLook;
+        const int n0 = s_m[0][z + 1][x], n1 = s_m[0][z + 1][x + 1], n2 = s_m[1][z + 1][x], n3 = s_m[1][z + 1][x + 1];
+        const bool same = m0 == m1 && m0 == m2 && m0 == m3 && m0 == n0 && m0 == n1 && m0 == n2 && m0 == n3;
+        const uint32_t code = same ? (uint32_t)m0 : (uint32_t)kPlaneLook;
         Plane d;
         d.x = __uint_as_float(__float_as_uint(s_d[0][z][x]) | (code & 8u) << 28);
         d.y = __uint_as_float(__float_as_uint(s_d[0][z][x + 1]) | (code & 4u) << 29);
         d.z = __uint_as_float(__float_as_uint(s_d[1][z][x]) | (code & 2u) << 30);
         d.w = __uint_as_float(__float_as_uint(s_d[1][z][x + 1]) | (code & 1u) << 31);
         const size_t at = ((size_t)(j + 1) * (C.nx + 1) + (i0 + x + 1)) * (C.nz + 2) + (p0 + z);
-        C.planes[at] = d;
+        __builtin_nontemporal_store(d, &C.planes[at]);   // (512 x 512 x 256: 427 us, 482 through the caches)
         if (C.codes) C.codes[at] = (uint16_t)(m0 | m1 << 4 | m2 << 8 | m3 << 12);
     }
 }

@@ -4,6 +4,8 @@ import pytest
 
 from paper_1204_6367_amd import workloads as W
 
+from test_gpu_raytrace import check_image
+
 pytestmark = pytest.mark.gpu
 
 
@@ -47,3 +49,24 @@ def test_lanes_per_ray(gpu, n_mat, shape, interp):
             one = gpu.Batch([vol], phys, [src], [jobs[k]]).primary(interp=interp)      # sixteen
             assert torch.equal(one[0], many[k]), (nu, k)
         assert float(sum(m.sum() for m in many)) > 0
+
+
+def test_records_with_rows_beyond_24_bits(gpu):
+    """A volume whose rows of plane records are 2^24 apart takes the full products: the oracle's
+    image, and with one, four and sixteen lanes per ray the same bits."""
+    import oracle
+    import torch
+    names = ["air", "soft_tissue", "bone"]
+    geom = W.Geometry(nu=9, nv=7, du_mm=40.0, dv_mm=40.0)
+    z, y, x = np.ogrid[0:4100, 0:2, 0:4100]
+    mat = (1 + ((z // 100 + x // 70 + y) % 2)).astype(np.uint8)
+    dens = np.broadcast_to(0.2 + 0.1 * np.sin(x / 300.0) + 0.05 * y, mat.shape).astype(np.float32)
+    ph = W.Phantom(dens, mat, (0.1, 150.0, 0.1), names)
+    prob = W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1)
+    vol, phys, src = gpu.upload(prob)
+    images = []
+    for n_jobs in (1, 100, 600):
+        jobs = [gpu.JobSpec(geom.replace(phi_rad=geom.phi_rad + 0.01 * k), 0, k) for k in range(n_jobs)]
+        images.append(gpu.Batch([vol], phys, [src], jobs).primary()[0].clone())
+    assert torch.equal(images[0], images[1]) and torch.equal(images[0], images[2])
+    check_image(images[0].cpu().numpy(), oracle.primary_raytrace(oracle.Problem.from_workload(prob)), "rows beyond 2^24")
