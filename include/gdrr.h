@@ -47,6 +47,9 @@
  * cells: the eight interpolation corners of the cell, the materials in their
  * sign bits).  Each call that takes a workspace reports the bytes it needs
  * through its own query (gdrr_*_workspace), sized for that call's arguments.
+ * The queries of the transport and the denoiser include a last part that only
+ * speeds a call up (a dispenser per XCD and the bounds of cubes for the single
+ * majorant: 35328 bytes; the images as float32): a call also runs without it.
  *
  * Errors: functions return GDRR_OK (0) or a negative code; no exception
  * crosses the ABI; gdrr_last_error() gives a message for the calling thread.
@@ -307,7 +310,7 @@ int gdrr_mc_trace(const gdrr_volume* vol, const gdrr_physics* phys, const gdrr_s
  * a ray may take at most 2^20 intervals.  Job k's image [nv][nu] (double)
  * goes to out + jobs[k].tally_offset; n_photons and job_id are ignored.
  * Flags: GDRR_INTERP_DENSITY, GDRR_ACCUMULATE (add to out); others are
- * rejected.  Workspace: gdrr_primary_workspace() bytes (it holds the cell
+ * rejected.  Workspace: gdrr_primary_workspace() bytes (it holds the plane
  * records of each volume when interpolating).  The timing hook brackets the
  * ray-tracing kernel.
  */
@@ -379,7 +382,9 @@ int gdrr_input_status(const void* workspace, void* stream);
 int gdrr_enable_timing(int enable);
 int gdrr_last_kernel_ms(float* ms);
 
-/* Default launch shape for this device (after gdrr_init). */
+/* Default launch shape for this device (after gdrr_init): that of launches whose
+ * volumes all track with local majorants; others take 256 lanes and waits of 32
+ * where the tuning leaves them to the library (0). */
 int gdrr_default_tuning(gdrr_tuning* out);
 
 /* Optional: binds the library to the current device and reads its properties. */

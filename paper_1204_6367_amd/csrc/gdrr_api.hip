@@ -1020,9 +1020,11 @@ RtLayout rt_carve(void* ws, const gdrr_volume* vols, int n_vols, const gdrr_phys
     }
     for (int v = 0; v < n_vols; ++v)
         if (volume_used(jobs, n_jobs, v)) {
+            // 18 bytes a plane of a column in the room of records of whole cells, 32 bytes each and
+            // one fewer per column: the size that callers know
             const size_t n = plane_count(vols[v].nx, vols[v].ny, vols[v].nz);
-            L.planes[v] = c.take<Plane>(n);
-            L.codes[v] = c.take<uint16_t>(n);
+            L.planes[v] = (Plane*)c.take<CellRec>(cell_count(vols[v]));
+            L.codes[v] = L.planes[v] ? (uint16_t*)(L.planes[v] + n) : nullptr;
         }
     L.bytes = c.off + 256;
     return L;
