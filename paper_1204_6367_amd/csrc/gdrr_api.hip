@@ -673,6 +673,24 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mfunc, block, held));
         return GDRR_OK;
     };
+    // The all-local adjoint's 71 VGPRs allow 6 wavefronts per SIMD where workgroups of 768 fit twice
+    // (25.6 ms; one of 1024 lanes per compute unit 30.7); the workgroup that keeps most lanes on
+    // a compute unit, the larger of equals.
+    if (wide && !tune.block && B.mode == kModeBackward) {
+        int most = 0, best = block;
+        n_slots = 32;
+        for (const int b : {1024, 768, 512}) {
+            int nb = 0;
+            block = b;
+            if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb))) return rc;
+            if (nb * b > most) {
+                most = nb * b;
+                best = b;
+            }
+        }
+        block = best;
+        n_slots = 64;
+    }
     // Started photons per wavefront: 64 (a full wavefront starts them), 32 where 64 would not fit
     // the LDS of a workgroup or would cost a workgroup per compute unit (8 against 6 wavefronts
     // per SIMD is worth 5 %, full against half wavefronts of starts 3 %), min_slots() where

@@ -1170,11 +1170,12 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeForward && LOCAL >= 3 ? 8 : 6)))
 }
 
 // The adjoint: at most 96 VGPRs (5 wavefronts per SIMD), where it would
-// otherwise take 97 and drop to 4; the all-local instantiation at most 64 (8
-// wavefronts per SIMD; it would take 70, and the 44 bytes it spills cost less
-// than the occupancy: 5.38e9 against 5.11e9 histories/s at 6).
+// otherwise take 97 and drop to 4; the all-local instantiation takes 71 of them and
+// runs 6 wavefronts in workgroups of 768.  Held to 64 for 8 wavefronts it spilled 40
+// bytes a lane in every flight (90 GB written by the adjoint of 9e8 histories): 1.8e8
+// histories of 256x256x160 voxels 28.4 ms against 25.6.
 template <int LOCAL>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(LOCAL >= 3 ? 8 : 5))) void mc_adjoint_kernel(
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void mc_adjoint_kernel(
     KParams P) {
     mc_body<kModeBackward, LOCAL>(P);
 }
