@@ -413,7 +413,7 @@ def rt_intervals(batch, dl_of):
 def raytrace_leg(wl, api, torch, steps, cpu):
     batch = wl["batch"]
     dl_of = lambda v: 0.5 * min(v.spacing_mm)
-    batch.primary()                                   # workspace and cell records
+    batch.primary()                                   # workspace and plane records
     torch.cuda.synchronize()
     ms, walls = [], []
     for _ in range(max(steps, 1)):

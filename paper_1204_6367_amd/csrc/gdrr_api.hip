@@ -76,6 +76,10 @@ struct Carver {
     }
 };
 
+// Workgroups of 1024 lanes for the rows of a source's spectrum table (a launch has fewer than 2^32
+// lanes, a table up to 2^24 rows).
+constexpr int kRowBlocks = 4096;
+
 // Rows of a source's spectrum table (one, or one per detector column); -1 if invalid.
 int spec_rows(const gdrr_source& s) {
     if (s.spec_rows == 0 || s.spec_rows == 1) return 1;
@@ -830,10 +834,11 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         const SrcArea& A = L.src[s];
         const int rows = spec_rows(S);
         const CdfTable flu{S.fluence, S.fu * S.fv, 1, A.flu_cdf, A.flu_guide, (int)A.flu_k};
-        const SrcPrepParams sp{{{S.spec_prob, S.n_spec, rows, A.spec_cdf, A.spec_guide, (int)A.spec_k}, flu}, status};
+        const int row_blocks = std::min(rows, kRowBlocks);
+        const SrcPrepParams sp{{{S.spec_prob, S.n_spec, rows, A.spec_cdf, A.spec_guide, (int)A.spec_k}, flu}, row_blocks, status};
         const bool is_long = flu.n > kLongTable;
         const unsigned blocks = is_long ? kSegs / kSegBlock : 1;
-        ls.push_back(make_launch((const void*)&cdf_kernel, dim3(rows + blocks), dim3(kSegs), 0, sp));
+        ls.push_back(make_launch((const void*)&cdf_kernel, dim3(row_blocks + blocks), dim3(kSegs), 0, sp));
         if (!is_long) continue;
         ls.push_back(make_launch((const void*)&long_cdf_kernel, dim3(blocks), dim3(kSegs), 0, LongCdfParams{flu, status}));
         ls.push_back(make_launch((const void*)&guide_kernel, dim3((A.flu_k + 255) / 256), dim3(256), 0, flu));
@@ -1208,10 +1213,10 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
     }
     for (int s = 0; s < n_srcs; ++s) {
         const gdrr_source& S = srcs[s];
-        RtPrepParams pp{S.spec_e_kev, S.spec_prob, S.fluence, S.n_spec, S.fu * S.fv, phys->mu_mass, phys->response,
+        RtPrepParams pp{S.spec_e_kev, S.spec_prob, S.fluence, S.n_spec, S.fu * S.fv, spec_rows(S), phys->mu_mass, phys->response,
                         phys->n_mat, phys->n_e, (double)phys->e0_kev, (double)phys->de_kev, L.coef[s], L.tab[s],
                         L.inv_wsum[s], status};
-        ls.push_back(make_launch((const void*)&raytrace_prep_kernel, dim3(spec_rows(S) + 1), dim3(kRtPrepBlock), 0, pp));
+        ls.push_back(make_launch((const void*)&raytrace_prep_kernel, dim3(std::min(spec_rows(S), kRowBlocks) + 1), dim3(kRtPrepBlock), 0, pp));
         rp.src[s] = RtSource{S.fluence, L.coef[s], L.tab[s], L.inv_wsum[s], S.n_spec, spec_rows(S)};
     }
     rp.jobs = L.jobs;
@@ -1354,15 +1359,23 @@ int run_denoise(const double* shat, long long stride, int n_img, int nv, int nu,
     d.inv_beta = 1.0f / beta;
     d.s_floor = s_floor;
     d.tiles_u = plan.tiles_u; d.tiles_v = plan.tiles_v; d.halo = plan.halo;
-    for (int p = 0; p < plan.passes; ++p) {
-        const bool last = p + 1 == plan.passes;
-        d.h_in = p > 0 ? hf : nullptr;
-        d.h_out = p == 0 && !last ? hf : nullptr;
-        d.s_in = p == 0 ? nullptr : pp[p & 1];
-        d.s_out = last ? nullptr : pp[(p + 1) & 1];
-        d.out = last ? out : nullptr;
-        d.iters = std::min(plan.sweeps, iters - p * plan.sweeps);
-        ls.push_back(make_launch(plan.kernel, dim3((unsigned)(n_img * plan.tiles_u * plan.tiles_v)), dim3(64 * plan.waves), 0, d));
+    // (a launch has fewer than 2^32 lanes)
+    const long long lanes = 64ll * plan.waves * plan.tiles_u * plan.tiles_v;
+    const int most = (int)std::max(1ll, std::min((long long)n_img, ((1ll << 32) - 1) / lanes));
+    for (int first = 0; first < n_img; first += std::min(most, n_img - first)) {
+        const size_t at = (size_t)first * (size_t)npix;
+        d.n_img = std::min(most, n_img - first);
+        d.shat = shat + (size_t)first * (size_t)stride;
+        for (int p = 0; p < plan.passes; ++p) {
+            const bool last = p + 1 == plan.passes;
+            d.h_in = p > 0 && hf ? hf + at : nullptr;
+            d.h_out = p == 0 && !last && hf ? hf + at : nullptr;
+            d.s_in = p == 0 ? nullptr : pp[p & 1] + at;
+            d.s_out = last ? nullptr : pp[(p + 1) & 1] + at;
+            d.out = last ? out + at : nullptr;
+            d.iters = std::min(plan.sweeps, iters - p * plan.sweeps);
+            ls.push_back(make_launch(plan.kernel, dim3((unsigned)(d.n_img * plan.tiles_u * plan.tiles_v)), dim3(64 * plan.waves), 0, d));
+        }
     }
     TimeEvents* ev = nullptr;
     {

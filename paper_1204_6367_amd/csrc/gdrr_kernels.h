@@ -1437,6 +1437,7 @@ constexpr int kLongTable = 2 * kSegs;
 
 struct SrcPrepParams {
     CdfTable t[2];            // the spectrum's rows, the fluence
+    int row_blocks;           // workgroups for the rows
     unsigned int* error;
 };
 
@@ -1505,10 +1506,16 @@ __device__ __forceinline__ void load_segments(const CdfTable& T, int first, int 
 __global__ __launch_bounds__(kSegs) void cdf_kernel(SrcPrepParams S) {
     __shared__ double part[kSegs];
     __shared__ SegTile tile;
-    const bool spectrum = (int)blockIdx.x < S.t[0].rows;
-    const CdfTable& T = spectrum ? S.t[0] : S.t[1];
-    const int block = spectrum ? blockIdx.x : blockIdx.x - S.t[0].rows;
-    if (spectrum || T.n <= kLongTable) return short_table(T, block, S.error, part);
+    if ((int)blockIdx.x < S.row_blocks) {
+        for (int row = blockIdx.x; row < S.t[0].rows; row += S.row_blocks) {
+            short_table(S.t[0], row, S.error, part);
+            __syncthreads();
+        }
+        return;
+    }
+    const CdfTable& T = S.t[1];
+    const int block = blockIdx.x - S.row_blocks;
+    if (T.n <= kLongTable) return short_table(T, block, S.error, part);
     const int per = (T.n + kSegs - 1) / kSegs, first = block * kSegBlock;
     double s = 0.0;
     bool bad = false;

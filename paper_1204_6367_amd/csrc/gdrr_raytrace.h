@@ -466,15 +466,15 @@ __global__ __launch_bounds__(256) void volume_check_kernel(VolCheckParams C) {
     if (err) atomicOr(C.error, err);
 }
 
-// Per source: the channel weights phi_k r(E_k) / sum phi (workgroup r: row r
-// of a joint source), the table 0.1 mu_tot(m, E_k) (linear in E between grid
+// Per source: the channel weights phi_k r(E_k) / sum phi (workgroup r: rows r, r + grid
+// - 1, ... of a joint source), the table 0.1 mu_tot(m, E_k) (linear in E between grid
 // points; workgroup 0) and 1 / sum w (the last workgroup, one CU's loads: 16 in
 // flight per lane: 256 x 192 weights 6.6 us, was 56 with 256 lanes and one load each).
 struct RtPrepParams {
     const float* spec_e;
     const float* spec_p;          // [rows][n_spec]
     const float* fluence;
-    int n_spec, npix;
+    int n_spec, npix, rows;
     const float* mu_mass;         // [n_mat][n_e][3]
     const float* response;        // [n_e] or null
     int n_mat, n_e;
@@ -489,58 +489,60 @@ constexpr int kRtPrepBlock = 1024;
 
 __global__ __launch_bounds__(kRtPrepBlock) void raytrace_prep_kernel(RtPrepParams R) {
     __shared__ double red[kRtPrepBlock];
-    const int row = blockIdx.x;
-    const bool fluence = row + 1 == (int)gridDim.x;
-    const float* phi = fluence ? R.fluence : R.spec_p + (size_t)row * R.n_spec;
-    const int n = fluence ? R.npix : R.n_spec;
-    double sum = 0.0;
-    bool bad = false;
-    int k = threadIdx.x;
-    for (; k + 15 * kRtPrepBlock < n; k += 16 * kRtPrepBlock) {    // 16 loads in flight
-        float v[16];
+    const bool fluence = blockIdx.x + 1 == gridDim.x;
+    for (int row = fluence ? R.rows - 1 : (int)blockIdx.x; row < R.rows; row += (int)gridDim.x - 1) {
+        const float* phi = fluence ? R.fluence : R.spec_p + (size_t)row * R.n_spec;
+        const int n = fluence ? R.npix : R.n_spec;
+        double sum = 0.0;
+        bool bad = false;
+        int k = threadIdx.x;
+        for (; k + 15 * kRtPrepBlock < n; k += 16 * kRtPrepBlock) {    // 16 loads in flight
+            float v[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = phi[k + u * kRtPrepBlock];
+            for (int u = 0; u < 16; ++u) v[u] = phi[k + u * kRtPrepBlock];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const double x = (double)v[u];
+            for (int u = 0; u < 16; ++u) {
+                const double x = (double)v[u];
+                bad = bad || !(x >= 0.0) || isinf(x);
+                sum += x;
+            }
+        }
+        for (; k < n; k += kRtPrepBlock) {
+            const double x = (double)phi[k];
             bad = bad || !(x >= 0.0) || isinf(x);
             sum += x;
         }
-    }
-    for (; k < n; k += kRtPrepBlock) {
-        const double x = (double)phi[k];
-        bad = bad || !(x >= 0.0) || isinf(x);
-        sum += x;
-    }
-    red[threadIdx.x] = sum;
-    __syncthreads();
-    for (int s = kRtPrepBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        red[threadIdx.x] = sum;
         __syncthreads();
-    }
-    const double psum = red[0];
-    if (bad || (threadIdx.x == 0 && !(psum > 0.0))) atomicOr(R.error, kErrWeights);
-    if (fluence) {
-        if (threadIdx.x == 0) R.inv_wsum[0] = psum > 0.0 ? 1.0 / psum : 0.0;
-        return;
-    }
-    float* coef = R.coef + (size_t)row * R.n_spec;
-    for (int k = threadIdx.x; k < R.n_spec; k += kRtPrepBlock) {
-        const double E = (double)R.spec_e[k];
-        const double g = (E - R.e0) / R.de;
-        int j = (int)floor(g);
-        j = j < 0 ? 0 : (j > R.n_e - 2 ? R.n_e - 2 : j);
-        const double f = g - (double)j;
-        double r = E;
-        if (R.response) r = (double)R.response[j] + f * ((double)R.response[j + 1] - (double)R.response[j]);
-        coef[k] = psum > 0.0 ? (float)((double)phi[k] / psum * r) : 0.0f;
-        if (row != 0) continue;
-        for (int m = 0; m < R.n_mat; ++m) {
-            const float* a = R.mu_mass + ((size_t)m * R.n_e + j) * 3;
-            const double ta = (double)a[0] + (double)a[1] + (double)a[2];
-            const double tb = (double)a[3] + (double)a[4] + (double)a[5];
-            R.tab[k * R.n_mat + m] = (float)(0.1 * (ta + f * (tb - ta)));
+        for (int s = kRtPrepBlock / 2; s > 0; s >>= 1) {
+            if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+            __syncthreads();
         }
+        const double psum = red[0];
+        if (bad || (threadIdx.x == 0 && !(psum > 0.0))) atomicOr(R.error, kErrWeights);
+        if (fluence) {
+            if (threadIdx.x == 0) R.inv_wsum[0] = psum > 0.0 ? 1.0 / psum : 0.0;
+            return;
+        }
+        float* coef = R.coef + (size_t)row * R.n_spec;
+        for (int k = threadIdx.x; k < R.n_spec; k += kRtPrepBlock) {
+            const double E = (double)R.spec_e[k];
+            const double g = (E - R.e0) / R.de;
+            int j = (int)floor(g);
+            j = j < 0 ? 0 : (j > R.n_e - 2 ? R.n_e - 2 : j);
+            const double f = g - (double)j;
+            double r = E;
+            if (R.response) r = (double)R.response[j] + f * ((double)R.response[j + 1] - (double)R.response[j]);
+            coef[k] = psum > 0.0 ? (float)((double)phi[k] / psum * r) : 0.0f;
+            if (row != 0) continue;
+            for (int m = 0; m < R.n_mat; ++m) {
+                const float* a = R.mu_mass + ((size_t)m * R.n_e + j) * 3;
+                const double ta = (double)a[0] + (double)a[1] + (double)a[2];
+                const double tb = (double)a[3] + (double)a[4] + (double)a[5];
+                R.tab[k * R.n_mat + m] = (float)(0.1 * (ta + f * (tb - ta)));
+            }
+        }
+        __syncthreads();
     }
 }
 

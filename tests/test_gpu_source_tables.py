@@ -6,6 +6,7 @@ import pytest
 from paper_1204_6367_amd import workloads as W
 
 from test_gpu_parity import compare_histories
+from test_gpu_raytrace import check_image
 
 pytestmark = pytest.mark.gpu
 
@@ -19,9 +20,10 @@ def gpu():
     return api
 
 
-# up to 2048 pixels in one workgroup, above in 16; segments of 1, 2, 3, 64, 65 and 68 pixels
+# up to 2048 pixels in one workgroup, above in 16; segments of 1, 2, 3, 64, 65 and 68 pixels;
+# up to 4096 rows of a joint source a workgroup each, above in turns
 @pytest.mark.parametrize("nu, nv, joint", [(1, 1, False), (3, 5, True), (32, 64, False), (2049, 1, False), (3, 683, True),
-                                           (83, 37, True), (256, 256, False), (257, 256, False), (67, 1031, False)])
+                                           (83, 37, True), (5000, 1, True), (256, 256, False), (257, 256, False), (67, 1031, False)])
 def test_photons_start_as_in_the_oracle(gpu, nu, nv, joint):
     import oracle
     rng = np.random.default_rng(nu + nv)
@@ -37,8 +39,11 @@ def test_photons_start_as_in_the_oracle(gpu, nu, nv, joint):
     prob = W.Problem(ph, W.physics_for(ph), W.Source(e, w, flu), geom, 30_000)
     vol, phys, src = gpu.upload(prob)
     g = gpu.trace(vol, phys, src, geom, prob.n_photons, seed=9)
-    frac, _ = compare_histories(g, oracle.mc_project(oracle.Problem.from_workload(prob), 9, prob.n_photons, trace=True))
+    o = oracle.Problem.from_workload(prob)
+    frac, _ = compare_histories(g, oracle.mc_project(o, 9, prob.n_photons, trace=True))
     assert frac >= 0.999
+    if joint:
+        check_image(gpu.primary(vol, phys, src, geom).cpu().numpy(), oracle.primary_raytrace(o), "joint")
 
 
 @pytest.mark.parametrize("nu, nv", [(5, 4), (100, 30)])
