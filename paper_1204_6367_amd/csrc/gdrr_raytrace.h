@@ -127,6 +127,17 @@ __device__ __forceinline__ void for_group(const F& f) {
     }
 }
 
+// The lanes of a ray share its LDS slots: what one wrote before this, another
+// reads after it (an order for the compiler; one wavefront's LDS accesses are
+// carried out in theirs).
+template <int G>
+__device__ __forceinline__ void rt_share() {
+    if constexpr (G > 1) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // G lanes per ray: lane l of a ray's group reads and interpolates intervals
 // j + l, and the group adds them in their order (every lane the same sums, the
 // ray's LDS slots written by one), so that the image does not depend on G.
@@ -170,6 +181,7 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
     float* Lm = rt_lds + ray;
     if (l == 0)
         for (int m = 0; m < P.n_mat; ++m) Lm[m * kRays] = 0.0f;
+    rt_share<G>();
 
     const DVolume& V = P.vol[J.vol];
     const float uc = ((float)iu + 0.5f - 0.5f * (float)J.nu) * J.du;
@@ -309,34 +321,38 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
                     const float hk = group_lane<G, k.value>(q.h), rk = group_lane<G, k.value>(rho);
                     if (mk >= 0) {
                         add_single(mk, hk, rk);
-                    } else if (mk == -1 && l == k.value) {
-                        const float gx0 = 1.0f - fx, gy0 = 1.0f - fy, gz0 = 1.0f - fz;
-                        const float wz0 = q.h * gz0, wz1 = q.h * fz;
-                        const float cd[8] = {c0, c1, c2, c3, c4, c5, c6, c7};
-                        if constexpr (G == 1) {
+                    } else if (mk == -1) {
+                        rt_share<G>();
+                        if (l == k.value) {
+                            const float gx0 = 1.0f - fx, gy0 = 1.0f - fy, gz0 = 1.0f - fz;
+                            const float wz0 = q.h * gz0, wz1 = q.h * fz;
+                            const float cd[8] = {c0, c1, c2, c3, c4, c5, c6, c7};
+                            if constexpr (G == 1) {
 #pragma unroll
-                            for (int c = 0; c < 8; ++c) {
-                                const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
-                                Lm[corner_material(c) * kRays] += wc * cd[c];
-                            }
-                        } else {
-                            // Material by material, each one's corners in their order.  left: a bit (the
-                            // highest) in the nibble of every corner still to add.
-                            const uint32_t cm = q.cm;
-                            uint32_t left = 0x88888888u;
-                            do {
-                                const uint32_t mat = (cm >> (__builtin_ctz(left) - 3)) & 15u;
-                                const uint32_t other = cm ^ (0x11111111u * mat);       // nibble 0: this material
-                                float sum = Lm[mat * kRays];
-    #pragma unroll
                                 for (int c = 0; c < 8; ++c) {
                                     const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
-                                    sum = __builtin_fmaf(wc, other & (15u << (4 * c)) ? 0.0f : cd[c], sum);
+                                    Lm[corner_material(c) * kRays] += wc * cd[c];
                                 }
-                                Lm[mat * kRays] = sum;
-                                left &= ((other & 0x77777777u) + 0x77777777u) | other;
-                            } while (left);
+                            } else {
+                                // Material by material, each one's corners in their order.  left: a bit (the
+                                // highest) in the nibble of every corner still to add.
+                                const uint32_t cm = q.cm;
+                                uint32_t left = 0x88888888u;
+                                do {
+                                    const uint32_t mat = (cm >> (__builtin_ctz(left) - 3)) & 15u;
+                                    const uint32_t other = cm ^ (0x11111111u * mat);       // nibble 0: this material
+                                    float sum = Lm[mat * kRays];
+#pragma unroll
+                                    for (int c = 0; c < 8; ++c) {
+                                        const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
+                                        sum = __builtin_fmaf(wc, other & (15u << (4 * c)) ? 0.0f : cd[c], sum);
+                                    }
+                                    Lm[mat * kRays] = sum;
+                                    left &= ((other & 0x77777777u) + 0x77777777u) | other;
+                                } while (left);
+                            }
                         }
+                        rt_share<G>();
                     }
                 });
             };
@@ -362,6 +378,7 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
         }
         if (cur >= 0 && l == 0) Lm[cur * kRays] += acc;
     }
+    rt_share<G>();
 
     float Lr[GDRR_MAX_MATERIALS];
 #pragma unroll
