@@ -417,6 +417,7 @@ struct PlaneParams {
     const uint8_t* material;
     int nx, ny, nz, n_mat;
     int tiles_x, tiles_z, tz;  // planes per tile (<= kPlZ)
+    unsigned int tiles;        // tiles_x tiles_z (ny + 1), taken in turns by the workgroups
     Plane* planes;
     uint16_t* codes;           // the four corners' materials, 4 bits each, or null
     unsigned int* error;       // input-error bits (invalid densities or materials)
@@ -425,43 +426,46 @@ struct PlaneParams {
 __global__ __launch_bounds__(256) void planes_kernel(PlaneParams C) {
     __shared__ float s_d[2][kPlZ + 1][kPlX + 1];
     __shared__ uint8_t s_m[2][kPlZ + 1][kPlX + 4];
-    const unsigned int tx = blockIdx.x % (unsigned)C.tiles_x, rest = blockIdx.x / (unsigned)C.tiles_x;
-    const int tz = (int)(rest % (unsigned)C.tiles_z), j = (int)(rest / (unsigned)C.tiles_z) - 1;
-    const int i0 = (int)tx * kPlX - 1;                         // the tile's first cell column
-    const int cols = min(kPlX, C.nx - i0);                     // columns i0 .. i0 + cols - 1 <= nx - 1
-    const int p0 = tz * C.tz, np = min(C.tz, C.nz + 2 - p0);   // planes p0 .. p0 + np - 1
     unsigned int err = 0u;
-    for (int e = threadIdx.x; e < 2 * (np + 1) * (cols + 1); e += 256) {        // (and the plane above the tile)
-        const int q = e / (cols + 1), x = e - q * (cols + 1);
-        const int r = q / (np + 1), z = q - r * (np + 1);
-        const int vx = min(max(i0 + x, 0), C.nx - 1), vy = min(max(j + r, 0), C.ny - 1);
-        const int vz = min(max(p0 + z - 1, 0), C.nz - 1);
-        const size_t v = ((size_t)vz * C.ny + vy) * C.nx + vx;
-        const float rho = C.density[v];
-        const int mr = C.material[v];
-        if (!density_ok(rho)) err |= kErrDensity;
-        if (mr >= C.n_mat) err |= kErrMaterial;
-        s_d[r][z][x] = fabsf(clean_density(rho));              // (-0 loses its sign too)
-        s_m[r][z][x] = (uint8_t)min(mr, C.n_mat - 1);
+    for (unsigned int tile = blockIdx.x; tile < C.tiles; tile += gridDim.x) {
+        const unsigned int tx = tile % (unsigned)C.tiles_x, rest = tile / (unsigned)C.tiles_x;
+        const int tz = (int)(rest % (unsigned)C.tiles_z), j = (int)(rest / (unsigned)C.tiles_z) - 1;
+        const int i0 = (int)tx * kPlX - 1;                         // the tile's first cell column
+        const int cols = min(kPlX, C.nx - i0);                     // columns i0 .. i0 + cols - 1 <= nx - 1
+        const int p0 = tz * C.tz, np = min(C.tz, C.nz + 2 - p0);   // planes p0 .. p0 + np - 1
+        for (int e = threadIdx.x; e < 2 * (np + 1) * (cols + 1); e += 256) {        // (and the plane above the tile)
+            const int q = e / (cols + 1), x = e - q * (cols + 1);
+            const int r = q / (np + 1), z = q - r * (np + 1);
+            const int vx = min(max(i0 + x, 0), C.nx - 1), vy = min(max(j + r, 0), C.ny - 1);
+            const int vz = min(max(p0 + z - 1, 0), C.nz - 1);
+            const size_t v = ((size_t)vz * C.ny + vy) * C.nx + vx;
+            const float rho = C.density[v];
+            const int mr = C.material[v];
+            if (!density_ok(rho)) err |= kErrDensity;
+            if (mr >= C.n_mat) err |= kErrMaterial;
+            s_d[r][z][x] = fabsf(clean_density(rho));              // (-0 loses its sign too)
+            s_m[r][z][x] = (uint8_t)min(mr, C.n_mat - 1);
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < cols * kPlZ; e += 256) {
+            const int x = e / kPlZ, z = e % kPlZ;
+            if (z >= np) continue;
+            const int m0 = s_m[0][z][x], m1 = s_m[0][z][x + 1], m2 = s_m[1][z][x], m3 = s_m[1][z][x + 1];
+            const int n0 = s_m[0][z + 1][x], n1 = s_m[0][z + 1][x + 1], n2 = s_m[1][z + 1][x], n3 = s_m[1][z + 1][x + 1];
+            const bool same = m0 == m1 && m0 == m2 && m0 == m3 && m0 == n0 && m0 == n1 && m0 == n2 && m0 == n3;
+            const uint32_t code = same ? (uint32_t)m0 : (uint32_t)kPlaneLook;
+            Plane d;
+            d.x = __uint_as_float(__float_as_uint(s_d[0][z][x]) | (code & 8u) << 28);
+            d.y = __uint_as_float(__float_as_uint(s_d[0][z][x + 1]) | (code & 4u) << 29);
+            d.z = __uint_as_float(__float_as_uint(s_d[1][z][x]) | (code & 2u) << 30);
+            d.w = __uint_as_float(__float_as_uint(s_d[1][z][x + 1]) | (code & 1u) << 31);
+            const size_t at = ((size_t)(j + 1) * (C.nx + 1) + (i0 + x + 1)) * (C.nz + 2) + (p0 + z);
+            __builtin_nontemporal_store(d, &C.planes[at]);   // (512 x 512 x 256: 427 us, 482 through the caches)
+            if (C.codes) C.codes[at] = (uint16_t)(m0 | m1 << 4 | m2 << 8 | m3 << 12);
+        }
+        __syncthreads();                                           // (before the next tile's voxels)
     }
     if (err) atomicOr(C.error, err);
-    __syncthreads();
-    for (int e = threadIdx.x; e < cols * kPlZ; e += 256) {
-        const int x = e / kPlZ, z = e % kPlZ;
-        if (z >= np) continue;
-        const int m0 = s_m[0][z][x], m1 = s_m[0][z][x + 1], m2 = s_m[1][z][x], m3 = s_m[1][z][x + 1];
-        const int n0 = s_m[0][z + 1][x], n1 = s_m[0][z + 1][x + 1], n2 = s_m[1][z + 1][x], n3 = s_m[1][z + 1][x + 1];
-        const bool same = m0 == m1 && m0 == m2 && m0 == m3 && m0 == n0 && m0 == n1 && m0 == n2 && m0 == n3;
-        const uint32_t code = same ? (uint32_t)m0 : (uint32_t)kPlaneLook;
-        Plane d;
-        d.x = __uint_as_float(__float_as_uint(s_d[0][z][x]) | (code & 8u) << 28);
-        d.y = __uint_as_float(__float_as_uint(s_d[0][z][x + 1]) | (code & 4u) << 29);
-        d.z = __uint_as_float(__float_as_uint(s_d[1][z][x]) | (code & 2u) << 30);
-        d.w = __uint_as_float(__float_as_uint(s_d[1][z][x + 1]) | (code & 1u) << 31);
-        const size_t at = ((size_t)(j + 1) * (C.nx + 1) + (i0 + x + 1)) * (C.nz + 2) + (p0 + z);
-        __builtin_nontemporal_store(d, &C.planes[at]);   // (512 x 512 x 256: 427 us, 482 through the caches)
-        if (C.codes) C.codes[at] = (uint16_t)(m0 | m1 << 4 | m2 << 8 | m3 << 12);
-    }
 }
 
 // Input check of a volume the ray tracer reads without plane records (no

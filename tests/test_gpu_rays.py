@@ -70,3 +70,23 @@ def test_records_with_rows_beyond_24_bits(gpu):
         images.append(gpu.Batch([vol], phys, [src], jobs).primary()[0].clone())
     assert torch.equal(images[0], images[1]) and torch.equal(images[0], images[2])
     check_image(images[0].cpu().numpy(), oracle.primary_raytrace(oracle.Problem.from_workload(prob)), "rows beyond 2^24")
+
+
+def test_more_cell_rows_than_a_launch_has_workgroups(gpu):
+    """2^24 rows of cells, a tile of plane records each: a launch of that many workgroups would
+    have 2^32 lanes.  Density linear in y, which 300 rows of 1 mm interpolate as well; float32 sums
+    of about 600 intervals (2^-24 each) over an optical depth of 4 differ by less than 2e-4."""
+    import torch
+    geom = W.Geometry(nu=17, nv=3, du_mm=20.0, dv_mm=20.0)
+    images = []
+    for ny in (300, 1 << 24):
+        dy = 300.0 / ny
+        y = (torch.arange(ny, device="cuda", dtype=torch.float64) + 0.5) * dy
+        dens = (0.5 + y / 300.0).float().reshape(1, ny, 1)
+        mat = torch.ones((1, ny, 1), dtype=torch.uint8, device="cuda")
+        small = W.Phantom(np.ones((1, 1, 1), np.float32), np.ones((1, 1, 1), np.uint8), (1.0, 1.0, 1.0), ["air", "soft_tissue"])
+        _, phys, src = gpu.upload(W.Problem(small, W.physics_for(small), W.pelvis_source(geom), geom, 1))
+        vol = gpu.DeviceVolume(dens, mat, (150.0, dy, 200.0))
+        images.append(gpu.Batch([vol], phys, [src], [gpu.JobSpec(geom, 0, 0)]).primary(step_mm=0.25)[0].clone())
+    assert float(images[0].min()) > 0
+    assert float(((images[1] - images[0]) / images[0]).abs().max()) < 2e-4
