@@ -1201,7 +1201,7 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
             const int tx = (V.nx + 1 + kPlX - 1) / kPlX, tzs = (V.nz + 2 + kPlZ - 1) / kPlZ;
             const unsigned n = (unsigned)((size_t)tx * tzs * (V.ny + 1));     // (below 2^30)
             PlaneParams cp{V.density, V.material, V.nx, V.ny, V.nz, phys->n_mat, tx, tzs, (V.nz + 2 + tzs - 1) / tzs, n,
-                           L.planes[v], lanes > 1 ? L.codes[v] : nullptr, status};
+                           L.planes[v], L.codes[v], status};
             // (a launch has fewer than 2^32 lanes)
             ls.push_back(make_launch((const void*)&planes_kernel, dim3(std::min(n, 1u << 23)), dim3(256), 0, cp));
         } else if (volume_used(jobs, n_jobs, v)) {

@@ -45,7 +45,8 @@ struct RtSource {
 // planes k and k+1, 32 bytes in a row (planes run from -1 to nz).  The sign
 // bits (densities are >= 0; corner 0's the highest) of plane k carry the common
 // material of cell k's eight corners, or kPlaneLook where they differ or it is that
-// number: the materials are then read from the voxel array.
+// number: the materials are then the codes of planes k and k+1, 4 bits a corner in an
+// array of their own.
 //
 // Rays are nearly horizontal and a wavefront holds 4 detector columns of 16
 // rows, so its lanes read runs of z in 4 or so cell columns: about 20 cache
@@ -142,13 +143,15 @@ __device__ __forceinline__ void rt_share() {
 // j + l, and the group adds them in their order (every lane the same sums, the
 // ray's LDS slots written by one), so that the image does not depend on G.
 // Many rays take one lane each.  Few rays leave the chip idle, a lone wavefront
-// spending 0.6 us on each of a ray's 560 steps, a third of it in the path of mixed
-// cells, where it waits for the corners' materials one after the other: with G > 1
-// those come along with the corners (codes; with one lane per ray the bytes count,
-// 8.7 against 6.5 ms for 60 images of 512x512x256 voxels), and a mixed cell costs
-// two LDS updates instead of eight.  One 256x192 image of 256x256x160 voxels: 330 ->
-// 160 us at G = 4; one of 64x48 pixels 380 -> 98 us at G = 16.  M16 (G = 1): 16
-// materials, one of them kPlaneLook.  SMALL: no index of the plane records or their
+// spending 0.6 us on each of a ray's 560 steps: one 256x192 image of 256x256x160 voxels
+// 330 -> 138 us at G = 4; one of 64x48 pixels 380 -> 92 us at G = 16.
+// A mixed cell's materials come from the corner codes: along with the corners for G > 1,
+// where a wait costs more than the bytes, when such a cell is met for G = 1 (with every
+// interval 8.7 against 6.5 ms for 60 images of 512x512x256 voxels).  Read from the voxel
+// array, x fastest, they cost a wavefront of 16 rows as many lines as it has lanes: 64
+// images of 256x192 of 256x256x160 voxels 2820 -> 2440 us, 16 of the same phantom with noise
+// in 5 % of the materials 2330 -> 1255 (planes of whole cells, 8 x 8 pixels: 2074), in all
+// of them 6810 -> 1234.  M16 (G = 1): 16 materials, one of them kPlaneLook.  SMALL: no index of the plane records or their
 // rows' stride reaches 2^24, so a cell's number takes two 24-bit products (full ones cost
 // four instructions each) and floats hold every bound; with the material in the lower
 // plane's record alone, 8 of 75 instructions an interval: 64 images of 256x192 of 256x256x160
@@ -296,12 +299,6 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
                 if (G > 1) q.cm = *reinterpret_cast<const CodePair*>(codes + q.cell);
             };
             const auto add = [&](const Step& q) {
-                const auto corner_material = [&](int c) {
-                    const int x = min(max(q.ix + (c & 1), 0), nx - 1);
-                    const int y = min(max(q.iy + ((c >> 1) & 1), 0), ny - 1);
-                    const int z = min(max(q.iz + (c >> 2), 0), nz - 1);
-                    return min((int)mats[(long long)z * nxy + (long long)y * nx + x], n_mat - 1);
-                };
                 // the densities without their flag bits
                 const float c0 = fabsf(q.d0.x), c1 = fabsf(q.d0.y), c2 = fabsf(q.d0.z), c3 = fabsf(q.d0.w);
                 const float c4 = fabsf(q.d1.x), c5 = fabsf(q.d1.y), c6 = fabsf(q.d1.z), c7 = fabsf(q.d1.w);
@@ -310,13 +307,11 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
                 int m = plane_code(q.d0);
                 m = m != kPlaneLook ? m : -1;
                 m = q.h > 0.0f ? m : -2;
-                // (material kPlaneLook itself)
-                if (G > 1) {
-                    if (m == -1 && q.cm == 0x11111111u * (q.cm & 15u)) m = (int)(q.cm & 15u);
-                } else if (M16 && m == -1) {
-                    bool same = true;
-                    for (int c = 0; c < 8; ++c) same = same && corner_material(c) == kPlaneLook;
-                    m = same ? kPlaneLook : -1;
+                uint32_t cm = q.cm;
+                if (m == -1) {
+                    if (G == 1) cm = *reinterpret_cast<const CodePair*>(codes + q.cell);
+                    // (material kPlaneLook itself; without it nothing waits for the codes here)
+                    if ((G > 1 || M16) && cm == 0x11111111u * (cm & 15u)) m = (int)(cm & 15u);
                 }
                 const float a00 = c0 + fx * (c1 - c0), a01 = c2 + fx * (c3 - c2);
                 const float a10 = c4 + fx * (c5 - c4), a11 = c6 + fx * (c7 - c6);
@@ -333,16 +328,16 @@ __global__ __launch_bounds__(kRtBlock) void raytrace_kernel(RtParams P) {
                             const float gx0 = 1.0f - fx, gy0 = 1.0f - fy, gz0 = 1.0f - fz;
                             const float wz0 = q.h * gz0, wz1 = q.h * fz;
                             const float cd[8] = {c0, c1, c2, c3, c4, c5, c6, c7};
-                            if constexpr (G == 1) {
+                            if constexpr (G <= 4) {
 #pragma unroll
                                 for (int c = 0; c < 8; ++c) {
                                     const float wc = (c & 1 ? fx : gx0) * (c & 2 ? fy : gy0) * (c & 4 ? wz1 : wz0);
-                                    Lm[corner_material(c) * kRays] += wc * cd[c];
+                                    Lm[((cm >> (4 * c)) & 15u) * kRays] += wc * cd[c];
                                 }
                             } else {
-                                // Material by material, each one's corners in their order.  left: a bit (the
-                                // highest) in the nibble of every corner still to add.
-                                const uint32_t cm = q.cm;
+                                // Material by material, each one's corners in their order (the latency of two
+                                // LDS updates instead of eight: one 16 x 16 image 81 us against 87).  left: a bit
+                                // (the highest) in the nibble of every corner still to add.
                                 uint32_t left = 0x88888888u;
                                 do {
                                     const uint32_t mat = (cm >> (__builtin_ctz(left) - 3)) & 15u;
@@ -425,7 +420,7 @@ struct PlaneParams {
     int tiles_x, tiles_z, tz;  // planes per tile (<= kPlZ)
     unsigned int tiles;        // tiles_x tiles_z (ny + 1), taken in turns by the workgroups
     Plane* planes;
-    uint16_t* codes;           // the four corners' materials, 4 bits each, or null
+    uint16_t* codes;           // the four corners' materials, 4 bits each
     unsigned int* error;       // input-error bits (invalid densities or materials)
 };
 
@@ -467,7 +462,7 @@ __global__ __launch_bounds__(256) void planes_kernel(PlaneParams C) {
             d.w = __uint_as_float(__float_as_uint(s_d[1][z][x + 1]) | (code & 1u) << 31);
             const size_t at = ((size_t)(j + 1) * (C.nx + 1) + (i0 + x + 1)) * (C.nz + 2) + (p0 + z);
             __builtin_nontemporal_store(d, &C.planes[at]);   // (512 x 512 x 256: 427 us, 482 through the caches)
-            if (C.codes) C.codes[at] = (uint16_t)(m0 | m1 << 4 | m2 << 8 | m3 << 12);
+            C.codes[at] = (uint16_t)(m0 | m1 << 4 | m2 << 8 | m3 << 12);
         }
         __syncthreads();                                           // (before the next tile's voxels)
     }

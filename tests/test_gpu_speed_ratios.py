@@ -1,0 +1,55 @@
+"""Kernel times against each other, where a path was once far slower than its neighbour.
+Bounds lie between the two, and times are the shortest of several."""
+import pytest
+
+from paper_1204_6367_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1204_6367_amd import api
+    api.enable_timing(True)
+    yield api
+    api.enable_timing(False)
+
+
+def shortest(gpu, call, n=5):
+    call()
+    times = []
+    for _ in range(n):
+        call()
+        times.append(gpu.last_kernel_ms())
+    return min(times)
+
+
+def rays(gpu, shape, n_images, noise):
+    """16 or more images of 256 x 192 (one lane per ray) of an ellipsoid phantom, a share of its materials at random."""
+    import torch
+    nz, ny, nx = shape
+    ph = W.ellipsoid_phantom(shape, (400.0 / nz, 500.0 / ny, 500.0 / nx), 5, n_inner=6)
+    geom = W.Geometry()
+    vol, phys, src = gpu.upload(W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    at = torch.rand(vol.material.shape, device="cuda", generator=g) < noise
+    some = (torch.rand(vol.material.shape, device="cuda", generator=g) * len(ph.materials)).to(torch.uint8)
+    vol.material = torch.where(at, some, vol.material).contiguous()
+    return gpu.Batch([vol], phys, [src], [gpu.JobSpec(geom.replace(phi_rad=0.37 * k), 0, k) for k in range(n_images)])
+
+
+def test_cells_of_several_materials(gpu):
+    """Rays through noise take 1.6 times as long as through the phantom; 7.8 times with materials
+    read from the voxels one by one."""
+    clean, noisy = (rays(gpu, (160, 256, 256), 16, p) for p in (0.0, 1.0))
+    assert shortest(gpu, noisy.primary) < 3.5 * shortest(gpu, clean.primary)
+
+
+def test_nearest_voxel_rays(gpu):
+    """The nearest voxel's density costs no more than the interpolated one; 1.5 times as much
+    when the wavefronts lie across the voxel rows."""
+    b = rays(gpu, (64, 64, 64), 16, 0.0)
+    assert shortest(gpu, lambda: b.primary(interp=False)) < 1.25 * shortest(gpu, b.primary)
