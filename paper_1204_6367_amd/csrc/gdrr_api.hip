@@ -599,7 +599,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     const size_t one_wave = (size_t)(tune.block ? tune.block : 256) / 64;      // least slots of a launch
     const auto fits = [&](int kind, size_t records) {
         return slots_offset_bytes(table_floats2(n_mat, phys->n_e, n_maj) * 8 + records * lds_record_bytes(kind)) +
-               one_wave * min_slots(kind) * slot_bytes(kind) <= dev.lds_max;
+               one_wave * kMinSlots * slot_bytes(kind) <= dev.lds_max;
     };
     if (local) {
         size_t n = 0, padded = 0;
@@ -682,7 +682,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // a compute unit, the larger of equals.
     if (wide && !tune.block && B.mode == kModeBackward) {
         int most = 0, best = block;
-        n_slots = 32;
+        n_slots = kMinSlots;
         for (const int b : {1024, 768, 512}) {
             int nb = 0;
             block = b;
@@ -695,17 +695,16 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         block = best;
         n_slots = 64;
     }
-    // Started photons per wavefront: 64 (a full wavefront starts them), 32 where 64 would not fit
+    // Started photons per wavefront: 64 (a full wavefront starts them), kMinSlots where 64 would not fit
     // the LDS of a workgroup or would cost a workgroup per compute unit (8 against 6 wavefronts
-    // per SIMD is worth 5 %, full against half wavefronts of starts 3 %), min_slots() where
-    // nothing else fits; workgroups shrink only where that does not fit either.
+    // per SIMD is worth 5 %, full against half wavefronts of starts 3 %); workgroups shrink only
+    // where those do not fit either.
     {
         int nb_64 = 0, nb_32 = 0;
         if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb_64))) return rc;
-        n_slots = 32;
+        n_slots = kMinSlots;
         if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb_32))) return rc;
         if (nb_64 > 0 && (nb_64 >= nb_32 || (tune.blocks_per_cu && tune.blocks_per_cu <= nb_64))) n_slots = 64;
-        else if (nb_32 == 0) n_slots = min_slots(local_kind);
         while (!tune.block && block > 256 && lds_for(n_mat) > dev.lds_max) block /= 2;
     }
     int mask_rows = 0;

@@ -14,6 +14,7 @@
 #pragma once
 
 #include "gdrr_device.h"
+#include "gdrr_plan.h"
 
 namespace gdrr {
 
@@ -71,22 +72,6 @@ struct KParams {
 __host__ __device__ inline size_t table_floats2(int tot_rows, int n_e, int n_maj) {
     return (size_t)tot_rows * n_e + (size_t)n_maj * (n_e - 1);
 }
-
-// Bytes of cube records per cube in LDS: the all-local instantiations and the
-// screened one keep one word (the density bound, whose low 5 bits are zero,
-// with a table row there), the others the record as built.
-__host__ __device__ inline size_t lds_record_bytes(int local_kind) { return local_kind >= 3 ? 4 : 8; }
-
-// Per wavefront, after the tables and cube records: slots of started photons,
-// from a 16-byte boundary.  A slot is two 16-byte words (position and energy;
-// direction and aim pixel) and, where a volume may track with a single
-// majorant, the distance left to the box (4 bytes).  64 slots a wavefront, or
-// min_slots() (at most 1 KiB a wavefront) where the LDS does not hold them.
-__host__ __device__ inline size_t slots_offset_bytes(size_t tables_and_records_bytes) {
-    return (tables_and_records_bytes + 15) & ~(size_t)15;
-}
-__host__ __device__ inline uint32_t slot_bytes(int local_kind) { return local_kind == 3 || local_kind == 4 ? 32u : 36u; }
-__host__ __device__ inline int min_slots(int local_kind) { return local_kind == 3 || local_kind == 4 ? 32 : 16; }   // (powers of two)
 
 // The row field of an all-local LDS record: 31 = no row (the bound then comes
 // from the cube's material mask in its global record).
@@ -194,7 +179,7 @@ struct Photon {
 // photons of its chunk all at once.  in: the photon enters the phantom;
 // otherwise it reaches its aim pixel unscattered.
 struct Start {
-    float px, py, pz, dx, dy, dz, E, trem;
+    float tin, dx, dy, dz, E, trem;
     int pix;
     bool in;
 };
@@ -219,21 +204,18 @@ __device__ __forceinline__ Start start_state(const KParams& P, const DJob& J, co
     s.dx = dx; s.dy = dy; s.dz = dz;
     s.E = fminf(fmaxf(S.spec_e[ke], P.e0), P.e_max);
     s.pix = kf;
-    s.px = s.py = s.pz = s.trem = 0.0f;
-    float tin, tout;
-    s.in = box_entry(V, J.Sx, J.Sy, J.Sz, dx, dy, dz, tin, tout);
-    if (s.in) {
-        s.px = J.Sx + tin * dx;
-        s.py = J.Sy + tin * dy;
-        s.pz = J.Sz + tin * dz;
-        s.trem = tout - tin;
-    }
+    float tout;
+    s.in = box_entry(V, J.Sx, J.Sy, J.Sz, dx, dy, dz, s.tin, tout);
+    s.trem = tout - s.tin;
     return s;
 }
 
-// A lane takes a started photon.
-__device__ __forceinline__ void take_start(const KParams& P, const Tables& T, int vol_off, Photon& ph, const Start& s) {
-    ph.px = s.px; ph.py = s.py; ph.pz = s.pz;
+// A lane takes a started photon of job J (one that misses the phantom is nowhere in it).
+__device__ __forceinline__ void take_start(const KParams& P, const Tables& T, const DJob& J, int vol_off, Photon& ph,
+                                           const Start& s) {
+    ph.px = __builtin_fmaf(s.tin, s.dx, J.Sx);
+    ph.py = __builtin_fmaf(s.tin, s.dy, J.Sy);
+    ph.pz = __builtin_fmaf(s.tin, s.dz, J.Sz);
     ph.dx = s.dx; ph.dy = s.dy; ph.dz = s.dz;
     ph.E = s.E;
     ph.trem = s.trem;
@@ -247,8 +229,9 @@ __device__ __forceinline__ void take_start(const KParams& P, const Tables& T, in
 
 __device__ __forceinline__ bool start_photon(const KParams& P, const Tables& T, const DVolume& V, int vol_off,
                                              Photon& ph) {
-    const Start s = start_state(P, P.jobs[ph.job], V, ph.pid);
-    take_start(P, T, vol_off, ph, s);
+    const DJob& J = P.jobs[ph.job];
+    const Start s = start_state(P, J, V, ph.pid);
+    take_start(P, T, J, vol_off, ph, s);
     return s.in;
 }
 
@@ -964,13 +947,13 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
     // the slots of started photons (offset in bytes from the LDS base of the first wavefront's)
     const uint32_t slots_off = (uint32_t)slots_offset_bytes(
         table_floats2(P.tot_rows, P.n_e, P.n_maj) * 8 + (size_t)P.macro_lds_n * lds_record_bytes(LOCAL));
-    // this wavefront's slots (wavefront-uniform): position words, direction words, distances
+    // this wavefront's slots (wavefront-uniform): directions and pixels, entries and energies, distances
     const uint32_t n_slots = (uint32_t)P.n_slots;
     const uint32_t wave_off =
         __builtin_amdgcn_readfirstlane((int)(slots_off + (threadIdx.x >> 6) * n_slots * slot_bytes(LOCAL)));
-    float4* const slot_p = reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + wave_off);
-    float4* const slot_d = slot_p + n_slots;
-    float* const slot_t = reinterpret_cast<float*>(slot_d + n_slots);
+    float4* const slot_d = reinterpret_cast<float4*>(reinterpret_cast<char*>(lds) + wave_off);
+    float2* const slot_e = reinterpret_cast<float2*>(slot_d + n_slots);
+    float* const slot_t = reinterpret_cast<float*>(slot_e + n_slots);
     bool no_rows = false;
     if (LOCAL >= 3) {
         // (the slots serve as scratch until the transport starts)
@@ -1088,13 +1071,13 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                                 Photon q;
                                 q.pid = pid;
                                 q.job = w_job;
-                                take_start(P, T, V.lds_majorant, q, s);
+                                take_start(P, T, J, V.lds_majorant, q, s);
                                 finish<MODE>(P, T, V, V.lds_majorant, q, kPrimary, q.pix0);
                             }
                             s.E = -1.0f;
                         }
                         const uint32_t k = pid & (n_slots - 1u);
-                        slot_p[k] = make_float4(s.px, s.py, s.pz, s.E);
+                        slot_e[k] = make_float2(s.tin, s.E);
                         slot_d[k] = make_float4(s.dx, s.dy, s.dz, __int_as_float(s.pix));
                         if (kTrem) slot_t[k] = s.trem;
                     }
@@ -1109,11 +1092,11 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                     ph.jid = P.jobs[w_job].job_id;
                     ph.passb = false;
                     const uint32_t k = ph.pid & (n_slots - 1u);
-                    const float4 a = slot_p[k], b = slot_d[k];
-                    if (a.w >= 0.0f) {
-                        const Start s{a.x, a.y, a.z, b.x, b.y, b.z, a.w, kTrem ? slot_t[k] : 0.0f,
-                                      __float_as_int(b.w), true};
-                        take_start(P, T, P.vol[w_vol].lds_majorant, ph, s);
+                    const float2 a = slot_e[k];
+                    const float4 b = slot_d[k];
+                    if (a.y >= 0.0f) {
+                        const Start s{a.x, b.x, b.y, b.z, a.y, kTrem ? slot_t[k] : 0.0f, __float_as_int(b.w), true};
+                        take_start(P, T, P.jobs[w_job], P.vol[w_vol].lds_majorant, ph, s);
                         ph.st = kFly;
                     }
                 }
