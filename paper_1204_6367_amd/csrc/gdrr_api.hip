@@ -136,11 +136,6 @@ int screen_cube_of(const gdrr_volume& v, size_t most) {
 #endif
 constexpr size_t kMacroLdsMax = GDRR_MACRO_LDS_MAX;   // bytes of cube records staged in LDS
 constexpr size_t kPaddedLdsMax = 112 << 10;            // the same with the padding of all-local grids
-// LDS allocation granule of a gfx950 workgroup (160 KiB / 128), as measured by
-// calib/lds_granule: three 512-thread workgroups share a compute unit up to 42
-// granules (53760 bytes) each, where hipOccupancyMaxActiveBlocksPerMultiprocessor
-// still reports three up to 54528.
-constexpr size_t kLdsGranule = 1280;
 
 int check_physics(const gdrr_physics* p) {
     if (!p) return fail(GDRR_EINVAL, "physics is NULL");
@@ -659,77 +654,39 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // (The trace kernel runs 6 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
     const bool wide = local_kind >= 3 && B.mode != kModeTrace;
     int block = tune.block ? tune.block : (wide ? 1024 : 256);
-    int n_slots = 64;
-    const auto lds_for = [&](int rows) {
-        return slots_offset_bytes(table_floats2(rows, phys->n_e, n_maj) * 8 +
-                                  (size_t)macro_lds_n * lds_record_bytes(local_kind)) +
-               (size_t)(block / 64) * n_slots * slot_bytes(local_kind);
-    };
-    // Rows for the material sets of cubes (all-local launches, at most 8 materials): as many
-    // as keep the workgroups per compute unit that the launch has without them (or the tuned
-    // count), as the runtime's occupancy calculation has it.
+    // Rows for the material sets of cubes: all-local and screened launches, at most 8 materials.
     const void* mfunc = mc_func_for(B.mode, local_kind);
-    // (the LDS of a workgroup is allocated in granules of kLdsGranule bytes, which the
-    // runtime's occupancy calculation does not round to: the query gets the rounded size)
-    const auto per_cu_with = [&](size_t bytes, int& nb) -> int {
-        nb = 0;
-        const size_t held = (bytes + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
-        GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, mfunc, block, held));
+    const int sets = local_kind >= 3 && n_mat <= 8 ? std::min((1 << n_mat) - 1 - n_mat, (int)kNoRow - n_mat) : 0;   // of two or more
+    const auto plan_for = [&](int threads, LdsPlan& plan) -> int {
+        int most = 0;
+        GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&most, mfunc, threads, 0));
+        plan = plan_lds(table_floats2(n_mat, phys->n_e, n_maj) * 8 + (size_t)macro_lds_n * lds_record_bytes(local_kind),
+                        (size_t)phys->n_e * 8, sets, local_kind == 5, threads / 64, slot_bytes(local_kind), dev.lds_max, std::max(most, 1),
+                        tune.blocks_per_cu);
         return GDRR_OK;
     };
-    // The all-local adjoint's 71 VGPRs allow 6 wavefronts per SIMD where workgroups of 768 fit twice
+    LdsPlan plan{};
+    if ((rc = plan_for(block, plan))) return rc;
+    // The all-local adjoint's 73 VGPRs allow 6 wavefronts per SIMD where workgroups of 768 fit twice
     // (25.6 ms; one of 1024 lanes per compute unit 30.7); the workgroup that keeps most lanes on
     // a compute unit, the larger of equals.
-    if (wide && !tune.block && B.mode == kModeBackward) {
-        int most = 0, best = block;
-        n_slots = kMinSlots;
-        for (const int b : {1024, 768, 512}) {
-            int nb = 0;
-            block = b;
-            if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb))) return rc;
-            if (nb * b > most) {
-                most = nb * b;
-                best = b;
+    if (wide && !tune.block && B.mode == kModeBackward)
+        for (const int b : {768, 512}) {
+            LdsPlan p{};
+            if ((rc = plan_for(b, p))) return rc;
+            if (p.per_cu * b > plan.per_cu * block) {
+                plan = p;
+                block = b;
             }
         }
-        block = best;
-        n_slots = 64;
+    // (the library's own workgroups shrink where they do not fit)
+    while (!tune.block && block > 256 && plan.per_cu == 0) {
+        block /= 2;
+        if ((rc = plan_for(block, plan))) return rc;
     }
-    // Started photons per wavefront: 64 (a full wavefront starts them), kMinSlots where 64 would not fit
-    // the LDS of a workgroup or would cost a workgroup per compute unit (8 against 6 wavefronts
-    // per SIMD is worth 5 %, full against half wavefronts of starts 3 %); workgroups shrink only
-    // where those do not fit either.
-    {
-        int nb_64 = 0, nb_32 = 0;
-        if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb_64))) return rc;
-        n_slots = kMinSlots;
-        if (lds_for(n_mat) <= dev.lds_max && (rc = per_cu_with(lds_for(n_mat), nb_32))) return rc;
-        if (nb_64 > 0 && (nb_64 >= nb_32 || (tune.blocks_per_cu && tune.blocks_per_cu <= nb_64))) n_slots = 64;
-        while (!tune.block && block > 256 && lds_for(n_mat) > dev.lds_max) block /= 2;
-    }
-    int mask_rows = 0;
-    if (local_kind >= 3 && n_mat <= 8 && lds_for(n_mat) <= dev.lds_max) {
-        int target = tune.blocks_per_cu;
-        if (!target && (rc = per_cu_with(lds_for(n_mat), target))) return rc;
-        const int sets = std::min((1 << n_mat) - 1 - n_mat, (int)kNoRow - n_mat);   // sets of two or more
-        for (int r = sets; r > 0; --r) {                       // the most rows that keep the target
-            if (lds_for(n_mat + r) > dev.lds_max) continue;
-            int nb = 0;
-            if ((rc = per_cu_with(lds_for(n_mat + r), nb))) return rc;
-            if (nb >= target) {
-                mask_rows = r;
-                break;
-            }
-        }
-    }
-    const size_t lds = lds_for(n_mat + mask_rows);
+    const size_t lds = plan.bytes;
     if (lds > dev.lds_max) return fail(GDRR_ENOTSUP, "tables exceed the LDS of a workgroup");
-    int per_cu = tune.blocks_per_cu;
-    if (!per_cu) {
-        int nb = 0;
-        if ((rc = per_cu_with(lds, nb))) return rc;
-        per_cu = std::max(nb, 1);
-    }
+    const int mask_rows = plan.rows, per_cu = tune.blocks_per_cu ? tune.blocks_per_cu : plan.per_cu;
     const unsigned grid = (unsigned)(dev.cus * per_cu);
     const unsigned long long waves = (unsigned long long)grid * (block / 64);
     int chunk = tune.chunk;
@@ -921,7 +878,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     kp.grad = B.grad;
     for (int v = 0; v < kMaxVol; ++v) kp.macro_lds[v] = v < GDRR_MAX_VOLUMES ? macro_lds[v] : -1;
     kp.macro_lds_n = macro_lds_n;
-    kp.n_slots = n_slots;
+    kp.n_slots = plan.slots;
     const void* mf = mc_func_for(B.mode, local_kind);
     int timed = -1;
     if (chunks > 0) {

@@ -25,3 +25,34 @@ def test_started_photons_take_a_kilobyte_a_wavefront(tmp_path):
     for n, size in rows:
         assert n >= 32 and n * size <= 16 * 64
         assert n * size % 16 == 0 and 64 * size % 16 == 0
+
+
+@pytest.mark.parametrize("words, waves, most, slot, least_rows", [
+    (1960, 8, 4, 24, 6), (1960, 4, 8, 24, 6), (3 * 1960, 8, 4, 24, 6), (3 * 1960, 16, 2, 24, 6),     # one and three phantoms, 40 mm cubes
+    (3564, 4, 8, 28, 2), (3564, 8, 4, 28, 6), (3564, 16, 2, 28, 6), (1960, 16, 1, 24, 6),     # (28 bytes: screened)
+    (28000, 16, 2, 24, 0), (40, 1, 32, 24, 0)])
+def test_rows_before_slots_before_workgroups(tmp_path, words, waves, most, slot, least_rows):
+    """4 materials on 299 energies (rows of 2392 bytes, 11 sets): room for half of the sets at the
+    price of slots, then of at most half of the workgroups (for two of them if a screened launch
+    would be left with fewer than 24 wavefronts); what is planned fits."""
+    row, lds = 299 * 8, 160 * 1024
+    fixed = 4 * row + 4 * words
+    for wanted in (0, 1, 2, 64):
+        (slots, rows, per_cu, size), = run_cpp(tmp_path, f"""
+            const LdsPlan p = plan_lds({fixed}, {row}, 11, {slot} == 28, {waves}, {slot}, {lds}, {most}, {wanted});
+            std::printf("%d %d %d %d\\n", p.slots, p.rows, p.per_cu, (int)p.bytes);""")
+        assert slots in (32, 64) and 0 <= rows <= 11 and 1 <= per_cu <= most
+        assert size == (fixed + rows * row + 15) // 16 * 16 + waves * slots * slot
+        assert per_cu * ((size + 1279) // 1280) <= 128
+        if wanted in (0, 1):
+            assert rows >= least_rows
+        if wanted == 0:
+            alone = (fixed + 15) // 16 * 16 + waves * 32 * slot
+            assert 2 * per_cu >= min(most, 128 // ((alone + 1279) // 1280))
+
+
+def test_what_does_not_fit_is_not_planned(tmp_path):
+    (slots, rows, per_cu, size), = run_cpp(tmp_path, """
+        const LdsPlan p = plan_lds(163000, 2392, 11, false, 4, 24u, 163840, 8, 0);
+        std::printf("%d %d %d %d\\n", p.slots, p.rows, p.per_cu, (int)p.bytes);""")
+    assert per_cu == 0 and size > 163840
