@@ -674,8 +674,12 @@ __device__ __forceinline__ bool walk_flight(const KParams& P, const DVolume& V, 
         const uint32_t row = rec & 31u;
         float tmax;
         if (NO_ROWS && row == kNoRow) {
+            // (quotients of whole numbers below 2^15 from their float reciprocals: the halves added are
+            // 2^-16 of the dividend from a whole quotient at least, the roundings 2^-22; with integer
+            // divisions 8e6 photons of 256x256x160 voxels of 9 materials took 2.41 ms, 2.16 now)
             const int c = (int)((ci - lds_address(lds_rec)) >> 2);
-            const int z = c / V.msz, y = (c - z * V.msz) / V.msy, x = c - z * V.msz - y * V.msy;
+            const int z = (int)(((float)c + 0.5f) * fast_rcp((float)V.msz)), r = c - z * V.msz;
+            const int y = (int)(((float)r + 0.5f) * fast_rcp((float)V.msy)), x = r - y * V.msy;
             tmax = set_bound(tot, P.tot_rows, V.macro[(z * V.mny + y) * V.mnx + x].y, f);
         } else {
             const float2 tt = tot[row];

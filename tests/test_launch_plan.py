@@ -56,3 +56,19 @@ def test_what_does_not_fit_is_not_planned(tmp_path):
         const LdsPlan p = plan_lds(163000, 2392, 11, false, 4, 24u, 163840, 8, 0);
         std::printf("%d %d %d %d\\n", p.slots, p.rows, p.per_cu, (int)p.bytes);""")
     assert per_cu == 0 and size > 163840
+
+
+@pytest.mark.parametrize("msy, msz", [(2, 4), (2, 6), (3, 9), (7, 49), (14, 140), (21, 462), (61, 4331), (514, 1028), (2, 1026), (14000, 28000)])
+def test_cube_numbers_from_float_reciprocals(msy, msz):
+    """A cube without a row finds its grid place by two divisions in float32: exact for every
+    word of a 112 KiB grid, with reciprocals up to 2 ulp off."""
+    import numpy as np
+    c = np.arange(28672)
+    f = np.float32
+    for ulp in (-2, -1, 0, 1, 2):
+        def quotient(n, d):
+            r = (np.array([f(1) / f(d)], f).view(np.int32) + np.int32(ulp)).view(f)[0]
+            return ((n.astype(f) + f(0.5)) * r).astype(np.int64)
+        z = quotient(c, msz)
+        y = quotient(c - z * msz, msy)
+        assert (z == c // msz).all() and (y == (c % msz) // msy).all()
