@@ -630,7 +630,16 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
                 screen_rec[v] = (uint2*)(extra + kDispBytes) + n;
                 n += cubes_of(B.vols[v], screen_cube[v]);
             }
-        if (has_extra && fits(5, n)) local_kind = 5;
+        // (and where the cubes' records would leave a caller's small workgroups fewer than 16 wavefronts
+        // per compute unit, and fewer than without: 256 lanes, waits 32, 6e6 photons of 64^3 voxels of 9
+        // materials 3.08 ms with 12 wavefronts screened, 2.55 with 20 unscreened; of 4 materials 2.14 with 16, 2.37)
+        const size_t threads = tune.block ? tune.block : B.mode == kModeTrace ? 256 : 1024;
+        const auto waves = [&](int kind, size_t records) {
+            const size_t bytes = slots_offset_bytes(table_floats2(n_mat, phys->n_e, n_maj) * 8 + records * lds_record_bytes(kind)) +
+                                 threads / 64 * kMinSlots * slot_bytes(kind);
+            return bytes > dev.lds_max ? 0 : dev.lds_max / ((bytes + kLdsGranule - 1) / kLdsGranule * kLdsGranule) * (threads / 64);
+        };
+        if (has_extra && fits(5, n) && (waves(5, n) >= 16 || waves(5, n) >= waves(0, 0))) local_kind = 5;
     }
     for (int v = 0; v < GDRR_MAX_VOLUMES; ++v) {
         macro_lds[v] = -1;
@@ -654,9 +663,11 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // (The trace kernel runs 6 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
     const bool wide = local_kind >= 3 && B.mode != kModeTrace;
     int block = tune.block ? tune.block : (wide ? 1024 : 256);
-    // Rows for the material sets of cubes: all-local and screened launches, at most 8 materials.
+    // Rows for the material sets of cubes: all-local and screened launches, at most 8 materials (screened
+    // ones have a row of all materials for the sets beyond, and for any with more materials).
     const void* mfunc = mc_func_for(B.mode, local_kind);
-    const int sets = local_kind >= 3 && n_mat <= 8 ? std::min((1 << n_mat) - 1 - n_mat, (int)kNoRow - n_mat) : 0;   // of two or more
+    const int sets = local_kind >= 3 && n_mat <= 8 ? std::min((1 << n_mat) - 1 - n_mat, (int)kNoRow - n_mat)   // of two or more
+                                                   : local_kind == 5;
     const auto plan_for = [&](int threads, LdsPlan& plan) -> int {
         int most = 0;
         GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&most, mfunc, threads, 0));

@@ -53,3 +53,26 @@ def test_nearest_voxel_rays(gpu):
     when the wavefronts lie across the voxel rows."""
     b = rays(gpu, (64, 64, 64), 16, 0.0)
     assert shortest(gpu, lambda: b.primary(interp=False)) < 1.25 * shortest(gpu, b.primary)
+
+
+def test_single_majorant_of_nine_materials(gpu):
+    """A single majorant of more than 8 materials is screened too: 1.4 times as long as with 4, 3.2 times
+    when every cube of several materials had its points tested."""
+    import numpy as np
+    import torch
+    shape = (160, 256, 256)
+    ph = W.ellipsoid_phantom(shape, (2.5, 1.95, 1.95), 5, n_inner=6)
+    geom = W.Geometry()
+    prob = W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1)
+    vol, phys, src = gpu.upload(prob)
+    n = len(ph.materials)
+    few = gpu.Batch([vol], phys, [src], [gpu.JobSpec(geom, 6_000_000, 0)])
+    more = W.Physics(np.concatenate([prob.physics.mu_mass] * 3)[:9], prob.physics.grid, None)
+    prob9 = W.Problem(ph, more, prob.source, geom, 1)
+    vol9, phys9, src9 = gpu.upload(prob9)
+    layer = (torch.arange(shape[2], device="cuda") // 8 % 3).to(torch.uint8) * n
+    vol9.material = ((vol9.material + layer) % 9).to(torch.uint8).contiguous()
+    many = gpu.Batch([vol9], phys9, [src9], [gpu.JobSpec(geom, 6_000_000, 0)])
+    times = [shortest(gpu, lambda b=b: b.project(seed=1, sumsq=False)) for b in (few, many)]
+    print(times)
+    assert times[1] < 2.2 * times[0]

@@ -119,3 +119,26 @@ def test_screened_flights_are_the_plain_ones(gpu, shape, n_mat, interp):
     got, ref = project_with(gpu, b, 0, 4, interp), project_with(gpu, b, EXTRA, 4, interp)
     assert float(ref.sum()) > 0
     assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("n_mat, tune", [(7, None), (8, None), (8, dict(block=512)), (9, dict(block=1024)), (16, None)])
+def test_screened_flights_with_more_sets_than_rows(gpu, n_mat, tune):
+    """Cubes of more sets of materials than the LDS has rows for (up to 247 of 8 materials, any of
+    more) are screened by the row of all materials: the histories of the plain flights."""
+    import torch
+    rng = np.random.default_rng(n_mat)
+    names = [["air", "soft_tissue", "bone", "lung", "aluminium", "water"][k % 6] for k in range(n_mat)]
+    shape = (24, 26, 28)
+    mat = np.zeros(shape, np.uint8)
+    for _ in range(300):                                   # boxes of one material
+        a = [int(rng.integers(0, s - 3)) for s in shape]
+        mat[a[0]:a[0] + 4, a[1]:a[1] + 4, a[2]:a[2] + 4] = rng.integers(0, n_mat)
+    dens = rng.uniform(0.01, 2.0, shape).astype(np.float32)
+    ph = W.Phantom(dens, mat, (7.0, 7.0, 7.0), names)
+    geom = W.Geometry(nu=30, nv=20, du_mm=8.0, dv_mm=8.0)
+    prob = W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1)
+    vol, phys, src = gpu.upload(prob)
+    b = gpu.Batch([vol], phys, [src], [gpu.JobSpec(geom.replace(phi_rad=0.5 * k), 30_001, k) for k in range(3)])
+    ref = project_with(gpu, b, EXTRA, 4, True)
+    got = b.project(seed=4, sumsq=True, tune=tune)
+    assert float(ref.sum()) > 0 and torch.equal(got, ref)
