@@ -521,11 +521,12 @@ int check_batch(const Batch& B) {
 // local: 0 single majorants, 1 local majorants with records in global memory, 2 with records in LDS,
 // 3 (4) every traced volume with local majorants and records in LDS, interpolated (nearest) density,
 // 5 every traced volume with a single majorant, screened (forward and trace: the adjoint visits null
-// collisions too)
+// collisions too); block: threads of a workgroup
 template <int MODE>
-const void* mc_func(int local) {
+const void* mc_func(int local, int block) {
     if constexpr (MODE == kModeBackward)
         return local == 4 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<4>)
+             : local == 3 && block > 768 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<3, 8>)
              : local == 3 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<3>)
              : local == 2 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<2>)
              : local == 1 ? reinterpret_cast<const void*>(&mc_adjoint_kernel<1>)
@@ -539,9 +540,9 @@ const void* mc_func(int local) {
                           : reinterpret_cast<const void*>(&mc_kernel<MODE, 0>);
 }
 
-const void* mc_func_for(int mode, int local) {
-    return mode == kModeForward ? mc_func<kModeForward>(local)
-         : mode == kModeTrace ? mc_func<kModeTrace>(local) : mc_func<kModeBackward>(local);
+const void* mc_func_for(int mode, int local, int block) {
+    return mode == kModeForward ? mc_func<kModeForward>(local, block)
+         : mode == kModeTrace ? mc_func<kModeTrace>(local, block) : mc_func<kModeBackward>(local, block);
 }
 
 // Does some job of the launch trace photons in volume v?
@@ -665,31 +666,35 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     int block = tune.block ? tune.block : (wide ? 1024 : 256);
     // Rows for the material sets of cubes: all-local and screened launches, at most 8 materials (screened
     // ones have a row of all materials for the sets beyond, and for any with more materials).
-    const void* mfunc = mc_func_for(B.mode, local_kind);
     const int sets = local_kind >= 3 && n_mat <= 8 ? std::min((1 << n_mat) - 1 - n_mat, (int)kNoRow - n_mat)   // of two or more
                                                    : local_kind == 5;
     const auto plan_for = [&](int threads, LdsPlan& plan) -> int {
         int most = 0;
-        GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&most, mfunc, threads, 0));
+        GDRR_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&most, mc_func_for(B.mode, local_kind, threads), threads, 0));
         plan = plan_lds(table_floats2(n_mat, phys->n_e, n_maj) * 8 + (size_t)macro_lds_n * lds_record_bytes(local_kind),
                         (size_t)phys->n_e * 8, sets, local_kind == 5, threads / 64, slot_bytes(local_kind), dev.lds_max, std::max(most, 1),
                         tune.blocks_per_cu);
         return GDRR_OK;
     };
     LdsPlan plan{};
-    if ((rc = plan_for(block, plan))) return rc;
-    // The all-local adjoint's 73 VGPRs allow 6 wavefronts per SIMD where workgroups of 768 fit twice
-    // (25.6 ms; one of 1024 lanes per compute unit 30.7); the workgroup that keeps most lanes on
-    // a compute unit, the larger of equals.
-    if (wide && !tune.block && B.mode == kModeBackward)
-        for (const int b : {768, 512}) {
+    // All-local adjoint: the widest of the workgroups that keep 6 wavefronts per SIMD, what its 73 VGPRs
+    // allow (1.8e8 histories of 256x256x160 voxels: 768 lanes 25.6 ms, 512 25.5, 1024 of 64 VGPRs with spills 28.4);
+    // 1024 only where the LDS leaves the others fewer lanes than that.
+    if (wide && !tune.block && B.mode == kModeBackward) {
+        plan = {};
+        int lanes = 0;
+        for (const int b : {768, 512, 1024}) {
             LdsPlan p{};
             if ((rc = plan_for(b, p))) return rc;
-            if (p.per_cu * b > plan.per_cu * block) {
+            if (std::min(p.per_cu * b, 1536) > lanes) {
+                lanes = std::min(p.per_cu * b, 1536);
                 plan = p;
                 block = b;
             }
         }
+    } else if ((rc = plan_for(block, plan))) {
+        return rc;
+    }
     // (the library's own workgroups shrink where they do not fit)
     while (!tune.block && block > 256 && plan.per_cu == 0) {
         block /= 2;
@@ -890,7 +895,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     for (int v = 0; v < kMaxVol; ++v) kp.macro_lds[v] = v < GDRR_MAX_VOLUMES ? macro_lds[v] : -1;
     kp.macro_lds_n = macro_lds_n;
     kp.n_slots = plan.slots;
-    const void* mf = mc_func_for(B.mode, local_kind);
+    const void* mf = mc_func_for(B.mode, local_kind, block);
     int timed = -1;
     if (chunks > 0) {
         timed = (int)ls.size();

@@ -1164,12 +1164,13 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeForward && LOCAL >= 3 ? 8 : 6)))
 }
 
 // The adjoint: at most 96 VGPRs (5 wavefronts per SIMD), where it would
-// otherwise take 97 and drop to 4; the all-local instantiation takes 71 of them and
-// runs 6 wavefronts in workgroups of 768.  Held to 64 for 8 wavefronts it spilled 40
-// bytes a lane in every flight (90 GB written by the adjoint of 9e8 histories): 1.8e8
-// histories of 256x256x160 voxels 28.4 ms against 25.6.
-template <int LOCAL>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void mc_adjoint_kernel(
+// otherwise take 97 and drop to 4; the all-local instantiation takes 73 of them and
+// runs 6 wavefronts in workgroups of up to 768.  Wider ones, which a caller may ask for, would fit a
+// compute unit once; for them (EU = 8) it is held to 64, two workgroups, with a spill of 40 bytes a lane in
+// every flight: 2e7 histories of 128x128x96 voxels, 1024 lanes, waits 8 and 12, 3.45 -> 2.94 ms (512 lanes or
+// 768 without spills 2.7; spilled and drawing photons ahead 3.74).
+template <int LOCAL, int EU = 5>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(EU))) void mc_adjoint_kernel(
     KParams P) {
     mc_body<kModeBackward, LOCAL>(P);
 }

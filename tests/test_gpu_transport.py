@@ -142,3 +142,24 @@ def test_screened_flights_with_more_sets_than_rows(gpu, n_mat, tune):
     ref = project_with(gpu, b, EXTRA, 4, True)
     got = b.project(seed=4, sumsq=True, tune=tune)
     assert float(ref.sum()) > 0 and torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("interp", [True, False])
+def test_adjoint_does_not_depend_on_the_workgroup(gpu, interp):
+    """The all-local adjoint at workgroups on both sides of 768 lanes, where another instantiation
+    takes over: the gradient up to the order of its float64 sums (fewer than 2^23 addends of
+    2^-53 each, relative to the sum of their sizes, which the largest entry bounds from below)."""
+    import torch
+    ph = W.ellipsoid_phantom((20, 22, 24), (12.0, 13.0, 14.0), 5, n_inner=4)
+    geom = W.Geometry(nu=32, nv=24, du_mm=12.0, dv_mm=12.0)
+    prob = W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1)
+    vol, phys, src = gpu.upload(prob)
+    vol.local_majorants(4, 0.1, 0.05)
+    b = gpu.Batch([vol], phys, [src], [gpu.JobSpec(geom, 200_003, 0)])
+    maj = torch.stack([gpu.majorant(vol, phys, interp, 0.1)])
+    adj = torch.ones(1, 2, 24, 32, dtype=torch.float64, device="cuda")
+    ref = b.backward(adj, maj, seed=5, interp=interp)
+    assert float(ref.abs().max()) > 0
+    for block in (256, 768, 832, 1024):
+        got = b.backward(adj, maj, seed=5, interp=interp, tune=dict(block=block))
+        assert float((got - ref).abs().max()) <= 2.0**-28 * float(ref.abs().max()), block
