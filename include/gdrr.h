@@ -382,9 +382,11 @@ int gdrr_input_status(const void* workspace, void* stream);
 int gdrr_enable_timing(int enable);
 int gdrr_last_kernel_ms(float* ms);
 
-/* Default launch shape for this device (after gdrr_init): that of launches whose
- * volumes all track with local majorants; others take 256 lanes and waits of 32
- * where the tuning leaves them to the library (0). */
+/* A launch shape that suits every kind of launch on this device (after gdrr_init):
+ * 256 lanes, waits of 32.  Fields left 0 (and a NULL tuning) are chosen launch by
+ * launch: 1024 lanes and waits of 8 and 12 for projections whose volumes all track
+ * with local majorants or all with a single one, 768 lanes and these waits for the
+ * adjoint with local majorants, else this shape (less where the LDS is short). */
 int gdrr_default_tuning(gdrr_tuning* out);
 
 /* Optional: binds the library to the current device and reads its properties. */

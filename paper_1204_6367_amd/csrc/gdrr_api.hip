@@ -655,12 +655,14 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         macro_lds[v] = macro_lds_n + (local_kind >= 3 ? outside_stride(cx, cy) : 0);
         macro_lds_n += local_kind >= 3 ? outside_stride(cx, cy) * (cz + 2) : cx * cy * cz;
     }
-    // Default shape.  All-local launches are bound by VALU issue: they gain from early refills
-    // and from 1024-thread workgroups, two per compute unit, which share the tables and cube
-    // records and so keep 8 wavefronts per SIMD (2e7 photons of a 256x256x160 phantom: 3.44 ms
-    // against 5.18 at 256 threads and deferral 32; 3.5 against 5.1 to 5.3 from 32x32x20 to
-    // 512x512x256).  A launch with a single-majorant volume waits on its gathers, where late
-    // refills do best (512x512x256: 3.21 ms against 3.50).
+    // Default shape.  All-local and screened launches are bound by VALU issue: they gain from early
+    // refills and from 1024-thread workgroups, two per compute unit, which share the tables and cube
+    // records and so keep 8 wavefronts per SIMD.  All-local (2e7 photons of a 256x256x160
+    // phantom): 2.50 ms against 4.46 at 256 threads, waits 32.  Screened (1e7 photons), ms at 256/32/32,
+    // 512/16/16, 1024/16/16, 1024/8/12: 64x64x64 3.75 2.37 1.92 1.86, 128x128x96 3.63 2.44 2.01 1.92,
+    // 256x256x160 4.75 2.43 1.93 1.86, 512x512x256 4.25 2.55 2.04 1.99; 1e5 photons 238 to 396 us at
+    // 256/32/32, 199 to 230 at 1024/8/12.  Launches that take neither path wait on their gathers,
+    // where late refills do best (512x512x256, unscreened: 3.21 ms against 3.50).
     // (The trace kernel runs 6 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
     const bool wide = local_kind >= 3 && B.mode != kModeTrace;
     int block = tune.block ? tune.block : (wide ? 1024 : 256);
@@ -1430,12 +1432,11 @@ int gdrr_last_kernel_ms(float* ms) {
 
 int gdrr_default_tuning(gdrr_tuning* out) {
     if (!out) return fail(GDRR_EINVAL, "out is NULL");
-    // (of launches whose volumes all track with local majorants from LDS; others 256, 32, 32)
-    out->block = 1024;
+    out->block = 256;
     out->blocks_per_cu = 0;
     out->chunk = 0;
-    out->defer = 8;
-    out->coll_defer = 12;
+    out->defer = 32;
+    out->coll_defer = 0;
     return GDRR_OK;
 }
 

@@ -72,3 +72,15 @@ def test_cube_numbers_from_float_reciprocals(msy, msz):
         z = quotient(c, msz)
         y = quotient(c - z * msz, msy)
         assert (z == c // msz).all() and (y == (c % msz) // msy).all()
+
+
+def test_default_tuning_is_a_shape_for_every_launch():
+    """What gdrr_default_tuning returns may be passed to any call: not the shape of one kind of launch."""
+    import ctypes as C
+
+    from paper_1204_6367_amd import _abi
+    if not os.path.exists(_abi.LIB_PATH):
+        build.build()
+    t = _abi.Tuning()
+    assert _abi.lib().gdrr_default_tuning(C.byref(t)) == 0
+    assert (t.block, t.blocks_per_cu, t.chunk, t.defer, t.coll_defer) == (256, 0, 0, 32, 0)
