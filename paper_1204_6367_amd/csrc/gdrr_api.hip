@@ -419,18 +419,20 @@ int add_setup(std::vector<Launch>& ls, const std::vector<FillParams>& fills, con
 // A pass over a volume: its cell records (if cells is not null) and the maxima of its densities.
 Launch voxels_launch(const gdrr_volume& V, int n_mat, bool interp, int cus, CellRec* cells, bool maxima,
                      unsigned int* rho_max, unsigned int* present, unsigned int* status) {
-    const size_t blocks = ((size_t)(V.nx + 1) * (size_t)(V.ny + 1) + 255) / 256;
+    const size_t columns = (size_t)(V.nx + 1) * (size_t)(V.ny + 1), blocks = (columns + 255) / 256;
+    int seg_log = 8;
+    while (seg_log > 2 && ((size_t)1 << (seg_log - 1)) >= columns) --seg_log;
     // 2 cells in z per workgroup, so that the workgroups in flight write a few planes and not
     // columns all over the records (512 x 512 x 256: 560 us; 4 cells 619, 8 cells 648, 65 cells
     // 692); 4 with the maxima, which every workgroup has to hand in (64^3, no records: 8.7 us
     // against 10.9 with 2); more where the grid's 65535 in y would not do
     const int planes = std::max(maxima ? 4 : 2, (int)(((size_t)V.nz + 65535) / 65535));
-    const VoxelParams p{V.density, V.material, V.nx, V.ny, V.nz, n_mat, planes, cells, status, rho_max, present};
+    const VoxelParams p{V.density, V.material, V.nx, V.ny, V.nz, n_mat, planes, seg_log, cells, status, rho_max, present};
     const void* const f = !cells  ? (interp ? (const void*)&voxels_kernel<false, 2> : (const void*)&voxels_kernel<false, 1>)
                           : !maxima ? (const void*)&voxels_kernel<true, 0>
                           : interp  ? (const void*)&voxels_kernel<true, 2>
                                     : (const void*)&voxels_kernel<true, 1>;
-    return make_launch(f, dim3((unsigned)blocks, (unsigned)((V.nz + planes) / planes)), dim3(256), 0, p);
+    return make_launch(f, dim3((unsigned)blocks, (unsigned)((V.nz / planes + (256 >> seg_log)) >> (8 - seg_log))), dim3(256), 0, p);
 }
 
 // Lanes per cube of the local majorants: the large cubes of large volumes are few (13 x 13 x 7 of

@@ -76,3 +76,26 @@ def test_single_majorant_of_nine_materials(gpu):
     times = [shortest(gpu, lambda b=b: b.project(seed=1, sumsq=False)) for b in (few, many)]
     print(times)
     assert times[1] < 2.2 * times[0]
+
+
+def test_majorant_of_a_tall_volume(gpu):
+    """200000 voxels on top of each other cost what they cost in a row (5.4 times as much with one column
+    of cells per lane and the other lanes idle)."""
+    import torch
+    ph = W.ellipsoid_phantom((4, 4, 4), (10.0, 10.0, 10.0), 5, n_inner=1)
+    geom = W.Geometry()
+    _, phys, _ = gpu.upload(W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1))
+    times = []
+    for shape in ((1, 1, 200_000), (200_000, 1, 1)):
+        vol = gpu.DeviceVolume(torch.rand(shape, device="cuda"), torch.ones(shape, dtype=torch.uint8, device="cuda"), (1.0, 1.0, 1.0))
+        ms = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                gpu.majorant(vol, phys)
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        times.append(min(ms))
+    assert times[1] < 2.5 * times[0], times

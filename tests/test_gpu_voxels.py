@@ -90,3 +90,11 @@ def test_volumes_without_photons_are_checked(gpu, macro):
     one = gpu.Batch([vol], phys, [src], job)
     assert torch.equal(out, one.project(seed=3))
     one.input_status()
+
+
+@pytest.mark.parametrize("shape", [(1000, 1, 1), (513, 1, 2), (700, 3, 4), (300, 7, 9), (257, 11, 10), (130, 10, 15)])
+def test_tall_volumes(gpu, shape):
+    """Few columns (4 to 176 with the cells' margin): a workgroup's lanes lie above each other too."""
+    for interp in (True, False):
+        test_majorant_is_the_maximum(gpu, shape, interp)
+    test_histories_match_oracle(gpu, shape, 0)
