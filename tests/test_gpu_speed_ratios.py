@@ -99,3 +99,27 @@ def test_majorant_of_a_tall_volume(gpu):
             ms.append(a.elapsed_time(b))
         times.append(min(ms))
     assert times[1] < 2.5 * times[0], times
+
+
+def test_majorant_of_the_voxels_themselves(gpu):
+    """Without interpolation the maximum needs one read of each voxel: half of the time of the
+    neighbourhoods' maximum for a large volume, no less than it when every cell read its corners."""
+    import torch
+    ph = W.ellipsoid_phantom((4, 4, 4), (10.0, 10.0, 10.0), 5, n_inner=1)
+    geom = W.Geometry()
+    _, phys, _ = gpu.upload(W.Problem(ph, W.physics_for(ph), W.pelvis_source(geom), geom, 1))
+    shape = (256, 512, 512)
+    vol = gpu.DeviceVolume(torch.rand(shape, device="cuda"), torch.ones(shape, dtype=torch.uint8, device="cuda"), (1.0, 1.0, 1.0))
+    times = []
+    for interp in (True, False):
+        ms = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                gpu.majorant(vol, phys, interp)
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        times.append(min(ms))
+    assert times[1] < 0.8 * times[0], times
