@@ -65,10 +65,14 @@ __device__ __forceinline__ float dn_data(float h, float s) {
 // them all (whole images).
 // Two sweeps per turn of the loop, one downwards and one upwards: a row's new values go
 // to the registers that held its neighbour's old ones, and the second sweep brings them
-// back without moves (not for whole images, where it spilled).
+// back without moves (not for whole images, where that spilled).
+// Whole images of 64 and 256 columns are read and written from one pointer by uniform offsets: an
+// address for each row spilled 64 and 14 VGPRs around the loop (1000 images of 64x384, 30 sweeps, 429 -> 375 us).
+// With 128 columns that is kept, 24 VGPRs outside the loop: the loop that comes with one pointer
+// waits more (1000 images of 128x384, 256 sweeps, 4.18 ms, 4.45 without the spills; 8 sweeps 270 and 272 us).
 // Bound by VALU issue, about 10 instructions a pixel and sweep of which the reciprocal
 // counts four times, and for few regions by the barrier's round trip (0.25 us a sweep).
-// 256 sweeps: one 512 x 384 image 176 us, 460 with regions of 64 x 80 pixels on 4 wavefronts
+// 256 sweeps: one 512 x 384 image 167 us, 460 with regions of 64 x 80 pixels on 4 wavefronts
 // and halos of 8; one 256 x 192 image 155, 1160 in one workgroup; 360 of them 2140, one
 // workgroup each (2 x 256 x 4.2 us), 2390 with the comparison of dn_data; 64 sweeps of 60
 // images of 512 x 384: 512, was 815; 100 sweeps of 2000 images of 64 x 48: 310, was 1220.
@@ -76,7 +80,7 @@ template <int C, int R, int RL, bool EDGE, bool SEL>
 __global__ __launch_bounds__(64 * kDnMaxWaves) void denoise_tile_kernel(DnParams D) {
     __shared__ float edge[2][2][kDnMaxWaves][64 * C];
     __shared__ float4 h_lds[RL ? RL : 1][RL ? kDnMaxWaves : 1][RL ? 16 * C : 1];   // [row][wavefront][lane's C values]
-    constexpr bool WHOLE = RL > 0;                         // the image is one region exactly
+    constexpr bool WHOLE = RL > 0, ONE = WHOLE && C != 2;  // the image is one region exactly; and from one pointer
     const int waves = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int cols = 64 * C, rows = R * waves;
     const int per_img = D.tiles_u * D.tiles_v;
@@ -92,6 +96,7 @@ __global__ __launch_bounds__(64 * kDnMaxWaves) void denoise_tile_kernel(DnParams
     const double* H = D.shat + (size_t)img * D.shat_stride;
     const float* Hf = D.h_in ? D.h_in + (size_t)img * npix : nullptr;
     const float* Sin = D.s_in ? D.s_in + (size_t)img * npix : nullptr;
+    const double* const Hw = H + (size_t)r0 * D.nu + c0;
     float s[R][C], h[R - RL][C];
     float* const hl = reinterpret_cast<float*>(&h_lds[0][RL ? wave : 0][0]) + lane * C;   // row k at hl[k kDnMaxWaves 64 C]
 #pragma unroll
@@ -101,7 +106,7 @@ __global__ __launch_bounds__(64 * kDnMaxWaves) void denoise_tile_kernel(DnParams
             // (EDGE: rows and columns beyond the image repeat its last ones)
             const int y = EDGE ? min(r0 + k, D.nv - 1) : r0 + k, x = EDGE ? min(c0 + c, D.nu - 1) : c0 + c;
             const size_t p = (size_t)y * D.nu + x;
-            const float hv = !WHOLE && Hf ? Hf[p] : (float)H[p];
+            const float hv = ONE ? (float)Hw[(size_t)k * D.nu + c] : !WHOLE && Hf ? Hf[p] : (float)H[p];
             if (k < RL) hl[k * kDnMaxWaves * 64 * C + c] = hv;
             else h[k - RL][c] = hv;
             s[k][c] = !WHOLE && Sin ? Sin[p] : fmaxf(hv, D.s_floor);
@@ -161,11 +166,16 @@ __global__ __launch_bounds__(64 * kDnMaxWaves) void denoise_tile_kernel(DnParams
             sweep(std::false_type{}, 1);
         }
     }
+    double* const Dw = ONE ? D.out + (size_t)img * npix + (size_t)r0 * D.nu + c0 : nullptr;
 #pragma unroll
     for (int k = 0; k < R; ++k)
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const int y = r0 + k, x = c0 + c;
+            if (ONE) {
+                Dw[(size_t)k * D.nu + c] = (double)s[k][c];
+                continue;
+            }
             if (!WHOLE && (y < vy0 || y >= vy1 || x < ux0 || x >= ux1)) continue;
             const size_t p = (size_t)img * npix + (size_t)y * D.nu + x;
             if (WHOLE || D.out) D.out[p] = (double)s[k][c];

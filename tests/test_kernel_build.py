@@ -34,3 +34,13 @@ def test_lanes_of_a_ray_share_their_slots_in_order(tmp_path):
     for name, body in re.findall(r"^define[^\n]*raytrace_kernelILi(\d+)E[^\n]*\{\n(.*?)^\}", out.read_text(), re.M | re.S):
         fences[int(name)] = len(re.findall(r'fence syncscope\("wavefront"\)', body))
     assert fences[1] == 0 and fences[4] >= 2 + 2 * 4 and fences[16] >= 2 + 2 * 16, fences
+
+
+def test_whole_images_of_64_and_256_columns_are_held_without_spills(tmp_path):
+    """A whole image in the registers of one workgroup (128 a lane) leaves none over: what the loads
+    and stores around the sweeps take decides whether any are spilled."""
+    use = "\n".join(f"template __global__ void gdrr::denoise_tile_kernel<{k}, false, {s}>(gdrr::DnParams);"
+                    for k in ("4, 12, 6", "1, 48, 24") for s in ("false", "true"))
+    said, _ = device_compile(tmp_path, '#include "gdrr_denoise.h"\n' + use, "-S", "-Rpass-analysis=kernel-resource-usage")
+    spills = re.findall(r"Function Name: \S*denoise_tile_kernel\S*.*?VGPRs Spill: (\d+)", said, re.S)
+    assert spills == ["0"] * 4, said[-3000:]
