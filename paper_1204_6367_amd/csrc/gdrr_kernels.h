@@ -1070,6 +1070,7 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
                 // and marked (E < 0).  (Started by the waiting lanes themselves, with only the draw
                 // done ahead: 13.0 against 12.5 ms for 7.6e7 photons of three phantoms.)
                 if ((uint32_t)n_dead > d_end - w_next && d_end < w_end) {
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");   // other lanes have read the slots filled now
                     const uint32_t room = n_slots - (d_end - w_next);
                     const uint32_t nd = w_end - d_end < room ? w_end - d_end : room;
                     if ((uint32_t)lane < nd) {
@@ -1155,8 +1156,9 @@ __device__ __forceinline__ void mc_body(const KParams& P) {
 }
 
 // The forward and trace transport: at most 80 VGPRs (6 wavefronts per SIMD);
-// the all-local forward at most 64 (8 wavefronts per SIMD, without spills),
-// which the 1024-thread workgroups, two per compute unit, then use.
+// the all-local and the screened forward at most 64 (61, 64 and 57: 8 wavefronts per SIMD),
+// which the 1024-thread workgroups, two per compute unit, then use.  No VGPR of theirs is
+// spilled to memory; 90, 124 and 42 scalars are, to lanes of VGPRs (a VALU instruction to get one back).
 template <int MODE, int LOCAL>
 __global__ __launch_bounds__(1024)
 __attribute__((amdgpu_waves_per_eu(MODE == kModeForward && LOCAL >= 3 ? 8 : 6))) void mc_kernel(KParams P) {
@@ -1164,8 +1166,8 @@ __attribute__((amdgpu_waves_per_eu(MODE == kModeForward && LOCAL >= 3 ? 8 : 6)))
 }
 
 // The adjoint: at most 96 VGPRs (5 wavefronts per SIMD), where it would
-// otherwise take 97 and drop to 4; the all-local instantiation takes 73 of them and
-// runs 6 wavefronts in workgroups of up to 768.  Wider ones, which a caller may ask for, would fit a
+// otherwise take 97 and drop to 4; the all-local instantiation takes 72 of them and
+// runs 6 wavefronts per SIMD in workgroups of 512 and 768.  Wider ones, which a caller may ask for, would fit a
 // compute unit once; for them (EU = 8) it is held to 64, two workgroups, with a spill of 40 bytes a lane in
 // every flight: 2e7 histories of 128x128x96 voxels, 1024 lanes, waits 8 and 12, 3.45 -> 2.94 ms (512 lanes or
 // 768 without spills 2.7; spilled and drawing photons ahead 3.74).
