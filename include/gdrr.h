@@ -227,10 +227,10 @@ size_t gdrr_mc_project_workspace(const gdrr_volume* vol, const gdrr_physics* phy
  * address is looked up once per device, by gdrr_init() or by the first call of
  * this function there.  Arguments and results are those of gdrr_mc_project,
  * bit for bit, with these differences:
- *  - a call whose gdrr_mc_project_workspace() exceeds GDRR_STATIC_SCRATCH_BYTES
- *    (about 4 million interpolation cells, e.g. 128x128x96 fits, 256x256x160
- *    does not), or that sets GDRR_RESUME, returns GDRR_EINVAL before any
- *    device work;
+ *  - a call whose gdrr_mc_project_workspace(), without its optional last part,
+ *    exceeds GDRR_STATIC_SCRATCH_BYTES (about 4 million interpolation cells, e.g.
+ *    128x128x96 fits, 256x256x160 does not), or that sets GDRR_RESUME, returns
+ *    GDRR_EINVAL before any device work;
  *  - the device-side input checks are not reported (gdrr_input_status needs a
  *    caller's workspace) and the timing hook is not applied.
  * Allocates no device memory and issues no host-to-device copy (the job's

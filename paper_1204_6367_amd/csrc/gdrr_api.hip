@@ -121,6 +121,8 @@ size_t cubes_of(const gdrr_volume& v, int m) {
 // only for want of what its layout needs): the chunk dispensers, and the records of the screening
 // cubes of a launch's single-majorant volumes.
 constexpr size_t kDispBytes = (size_t)kDispensers * kDispStride * sizeof(unsigned long long);
+// (16 KiB of LDS.  1e7 photons, ms with 512, 1024, 2048, 4096, 8192 cubes: 64x64x64 2.41 2.23 2.12 2.01 1.98,
+// 128x128x96 2.51 2.18 2.15 2.02 2.00, 256x256x160 2.25 2.23 1.96 1.92 1.96, 512x512x256 2.30 2.10 2.03 1.99 2.03)
 constexpr size_t kScreenCubes = 4096;
 constexpr size_t kExtraBytes = kDispBytes + kScreenCubes * sizeof(uint2) + 512;
 
@@ -435,8 +437,11 @@ Launch voxels_launch(const gdrr_volume& V, int n_mat, bool interp, int cus, Cell
     return make_launch(f, dim3((unsigned)blocks, (unsigned)((V.nz / planes + (256 >> seg_log)) >> (8 - seg_log))), dim3(256), 0, p);
 }
 
-// Lanes per cube of the local majorants: the large cubes of large volumes are few (13 x 13 x 7 of
-// 40^3 voxels: 1183 workgroups, 118 us with 1024 lanes, 315 with 256).
+// Lanes per cube of the local majorants and the screening: large cubes are few (13 x 13 x 7 of 40^3
+// voxels: 1183 workgroups, 118 us with 1024 lanes, 315 with 256), small ones have no work for more
+// than 256 lanes.  A call of 64 photons on 512x512x256 voxels, us with 256 and 1024 lanes at edges of
+// 4, 8, 12, 14, 20, 40 and 64: 2474 5936, 1388 1592, 1053 1076, 1036 1064, 955 984, 899 864, 1024 834; on
+// 256x256x160 617 1164, 367 416, 293 305, 269 268, 312 309, 309 282, 484 339.
 unsigned macro_block(int cube) { return cube > 12 ? 1024u : 256u; }
 
 struct Batch {
@@ -661,11 +666,11 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
     // refills and from 1024-thread workgroups, two per compute unit, which share the tables and cube
     // records and so keep 8 wavefronts per SIMD.  All-local (2e7 photons of a 256x256x160
     // phantom): 2.50 ms against 4.46 at 256 threads, waits 32.  Screened (1e7 photons), ms at 256/32/32,
-    // 512/16/16, 1024/16/16, 1024/8/12: 64x64x64 3.75 2.37 1.92 1.86, 128x128x96 3.63 2.44 2.01 1.92,
-    // 256x256x160 4.75 2.43 1.93 1.86, 512x512x256 4.25 2.55 2.04 1.99; 1e5 photons 238 to 396 us at
-    // 256/32/32, 199 to 230 at 1024/8/12.  Launches that take neither path wait on their gathers,
+    // 512/16/16, 1024/16/16, 1024/8/12: 64x64x64 3.43 2.16 1.93 1.86, 128x128x96 3.76 2.13 2.00 1.91,
+    // 256x256x160 3.76 2.31 1.92 1.86, 512x512x256 3.96 2.41 2.03 1.98; 1e5 photons 217 to 251 us at
+    // 256/32/32, 205 to 231 at 1024/8/12.  Launches that take neither path wait on their gathers,
     // where late refills do best (512x512x256, unscreened: 3.21 ms against 3.50).
-    // (The trace kernel runs 6 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
+    // (The trace kernel runs 7 wavefronts per SIMD, which 1024-thread workgroups would cut to 4.)
     const bool wide = local_kind >= 3 && B.mode != kModeTrace;
     int block = tune.block ? tune.block : (wide ? 1024 : 256);
     // Rows for the material sets of cubes: all-local and screened launches, at most 8 materials (screened
@@ -681,8 +686,7 @@ int run_batch(const Batch& B, void* ws, size_t ws_bytes, hipStream_t st) {
         return GDRR_OK;
     };
     LdsPlan plan{};
-    // All-local adjoint: the widest of the workgroups that keep 6 wavefronts per SIMD, what its 73 VGPRs
-    // allow (1.8e8 histories of 256x256x160 voxels: 768 lanes 25.6 ms, 512 25.5, 1024 of 64 VGPRs with spills 28.4);
+    // All-local adjoint: the widest of the workgroups that keep 6 wavefronts per SIMD (1.8e8 histories of 256x256x160 voxels: 768 lanes 25.6 ms, 512 25.5, 1024 of 64 VGPRs with spills 28.4);
     // 1024 only where the LDS leaves the others fewer lanes than that.
     if (wide && !tune.block && B.mode == kModeBackward) {
         plan = {};
