@@ -1033,9 +1033,10 @@ RtLayout rt_carve(void* ws, const gdrr_volume* vols, int n_vols, const gdrr_phys
     return L;
 }
 
-// Lanes per ray for a number of 16 x 16 tiles.  Measured (us, 1 / 4 / 16 lanes): 192 tiles 330 /
-// 163 / 226, 384 tiles 317 / 222 / 377, 768 tiles 440 / 530 / 970 (256x192 images of 256x256x160
-// voxels); 12 tiles 383 / 149 / 98, 48 tiles 406 / 159 / 139, 96 tiles 419 / 193 / 250 (64x48 images).
+// Lanes per ray for a number of 16 x 16 tiles.  Measured (us, 1 / 4 / 16 lanes, 256x256x160 voxels): 192 tiles
+// 329 / 138 / 204, 384 tiles 340 / 188 / 365, 576 tiles 393 / 319 / 582, 768 tiles 408 / 510 / 1078 (images of
+// 256x192); 12 tiles 432 / 156 / 91, 48 tiles 460 / 165 / 111, 96 tiles 449 / 169 / 132 (of 64x48): the lines
+// could lie up to half as far again to the right.
 int rt_lanes(unsigned long long tiles) { return tiles <= 64 ? 16 : tiles <= 512 ? 4 : 1; }
 
 constexpr unsigned kRtMaxTiles = (1u << 24) - 1024u;    // grid * block stays below 2^32 work-items
