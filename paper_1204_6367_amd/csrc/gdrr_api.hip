@@ -1214,7 +1214,12 @@ int run_primary(const gdrr_volume* vols, int n_vols, const gdrr_physics* phys, c
     if (grid * kRtBlock >= (1ull << 32)) return fail(GDRR_EINVAL, "too many pixels in one call (2^32 lanes)");
     const int timed = (int)ls.size();
     const void* const f = small ? rt_kernel<true>(lanes, phys->n_mat) : rt_kernel<false>(lanes, phys->n_mat);
-    ls.push_back(make_launch(f, dim3((unsigned)grid), dim3(kRtBlock), lds / lanes, rp));
+    // Nearest voxel, one lane per ray: seven workgroups per compute unit (by their LDS), not the eight that
+    // the registers allow.  Their lines of the voxel arrays are shared through L1 and L2, which eight
+    // overflow (us with 7 and 8, 4 images of 512x384 or 16 of 256x192: 512x512x256 voxels seen along x 2297 2805,
+    // 256x256x160 907 960 and 1126 1185, along y 719 689; 6 workgroups 2266, 964, 1228, 870).
+    const size_t rt_lds = lanes == 1 && !interp ? std::max(lds, 18 * kLdsGranule) : lds / lanes;
+    ls.push_back(make_launch(f, dim3((unsigned)grid), dim3(kRtBlock), rt_lds, rp));
     TimeEvents* ev = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_time_mu);
